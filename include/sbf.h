@@ -217,6 +217,8 @@ int sbf_get_variant(const sbf_filter *f);
  *     which the insert's repair walk uses as well;
  *   wide-shard kernels: 16 (default) or 32 for insert and query;
  *   run-time parameter kernels: 8 (default) or 16 for insert and query.
+ * A given insert length also keeps every insert on the family's own kernels;
+ * at the default, large inserts are binned (see SBF_INSERT_TWO_PASS).
  * Other values (and any value for the generic kernels) return SBF_E_INVAL.
  * The result does not depend on the tile size.  sbf_get_tile reads the
  * effective lengths back (0 for the generic kernels; pointers may be NULL;
@@ -229,7 +231,15 @@ int sbf_get_tile(const sbf_filter *f, uint32_t *insert_kmers_per_lane, uint32_t 
  *     segment's shard (stores that write through to the device's coherence
  *     point, so that racing updates only drop each other's bits), then a
  *     second pass over the same segments that atomically ORs back any bit a
- *     concurrent update overwrote;
+ *     concurrent update overwrote.  A batch that is large for the filter
+ *     (filters of at least 2^24 bits, H <= 8, k-m >= 5; from 131072 k-mers, and
+ *     one k-mer for every 112 to 256 bits of filters above 16 MiB) is binned
+ *     instead: its super-k-mers are sorted by shard range into device scratch
+ *     memory, about 1.2 times the filter's size plus 1 GiB at most (or 0.3 GB
+ *     for small filters), kept until the filter is destroyed, and every part
+ *     of the filter is then read and written once.  Without that much free
+ *     memory, or while the stream is being captured (other than by
+ *     sbf_graph_create), the two passes run;
  *   SBF_INSERT_ATOMIC: one 64-bit atomic OR per shard word, as in the paper's
  *     Algorithm 1.
  * Both produce the same filter; the generic kernel always uses atomics. */

@@ -1,0 +1,864 @@
+// Binned insert of large batches (shards of 4, 8 or 16 words, k <= 32, H <= 8)
+// for gfx950.
+//
+// The two-pass insert (kernels_rolling.hip and the other families) reads and
+// writes a random shard per super-k-mer, then reads every shard again to
+// restore the bits that racing writes dropped; it is bound by those random
+// accesses (a 128-byte line moves for every 32-byte shard).  For a batch that
+// touches most of the filter it is cheaper to bring the super-k-mers to the
+// filter in order:
+//   1. bin_kernel walks the sequence once, finds the super-k-mers (runs of
+//      valid k-mers with one shard) and appends each as a 16-byte record (its
+//      bases, length and shard) to the bucket of its shard range;
+//   2. split_kernel (filters of more than 256 slices) splits each bucket into
+//      slices of 64 KB of the filter;
+//   3. apply_kernel holds one slice in LDS, ORs the s-mer bits of the slice's
+//      records into it and writes the slice back once.
+// Every slice is read and written by one workgroup, so no update races with
+// another and no repair pass is needed.  A record that finds its bucket full
+// (a batch far from the expected spread over shards) is applied at once with
+// atomic ORs of the bits that are missing, before any slice is read.
+#include "sbf_device.h"
+#include "sbf_internal.h"
+#include "sbf_tiles.h"
+
+#include <algorithm>
+#include <cmath>
+
+namespace sbf {
+namespace {
+
+constexpr int kBinWG = 256;
+constexpr int kBinL = 32;                   // k-mers per lane
+constexpr int kBinTile = kBinWG * kBinL;    // k-mers per tile
+constexpr int kCountShift = 5;              // counters one 128-byte line apart
+constexpr int kXcds = 8;
+constexpr int kMaxBucketBits1 = 8;
+constexpr int kMaxBucketBits2 = 11;
+constexpr int kSplitWG = 512;
+constexpr int kSplitPer = 8;                // records per lane
+constexpr int kSplitTile = kSplitWG * kSplitPer;
+#ifndef SWB
+#define SWB 13
+#define AWG 512
+#define COH 1
+#endif
+constexpr int kSliceWordBits = SWB;          // a slice is 2^13 words: 64 KB
+constexpr int kSliceWords = 1 << kSliceWordBits;
+constexpr uint32_t kApplyGrid = 512 << (13-SWB);        // two workgroups per CU (64 KB of LDS each)
+
+// k-mers binned at a time: at least these (0.3 GB of records at w = 16), more
+// for a filter that has more memory itself
+constexpr uint64_t kMinChunkKmers = 1ull << 27;
+// batches up to these append to one part per bucket
+constexpr uint64_t kOnePartKmers = 1ull << 25;
+constexpr int kMinSliceBits = 6;  // fewer slices leave most of the GPU idle
+// Batches that take the binned insert.  It reads and writes the whole filter,
+// so it needs enough k-mers for the filter's size; measured (us, binned against
+// two passes) at (31,28,16,4): 2^27 bits 0.15M k-mers 43/53, 4M 57/127; 2^28
+// bits 1M 62/63, 2M 64/73; 2^31 bits 8M 162/143, 16M 184/228, 128M 496/1057;
+// 2^33 bits 32M 547/404, 64M 638/683; 2^36 bits 400M 4804/3938.  The other
+// kernel families' two passes take twice as long: at (31,26,16,4) 2^26 bits
+// 0.15M 30/39; 2^27 bits 0.25M 43/41, 0.5M 42/49; 2^31 bits 4M 156/156, 8M
+// 164/235; 2^33 bits 32M 547/723; 2^36 bits 256M 4271/5071; 16-word shards
+// at (31,28,16,4) 2^31 bits 8M 167/259, 2^36 bits 256M 4277/5586.
+constexpr uint64_t kMinBinnedKmers = 1ull << 17;
+constexpr uint64_t kLaneSmallBits = 1ull << 27, kOtherSmallBits = 1ull << 26;
+constexpr uint64_t kLaneBitsPerKmer = 112, kOtherBitsPerKmer = 256;
+
+// A super-k-mer of at most 16 k-mers: its bases from the top of x down (2 bits
+// each, at most 46), its number of k-mers minus one in the low 4 bits of z,
+// its shard in w.
+typedef u32x4 Record;
+
+// Run-time geometry of the records' bits.
+struct BitGeo {
+  int z;        // k - s
+  int s_shift;  // 64 - 2s
+  int H;
+  int slice;    // 64 / H
+  int sw_log2;  // log2 of the words per shard
+};
+
+struct BinGeo {
+  int k;
+  int m_shift;  // 32 - 2m for m <= 16, 64 - 2m above
+  int nmax;     // k-mers per record
+  uint32_t shard_mask;
+  int bucket_shift;  // shard >> bucket_shift = bucket
+  int nbuckets;
+  int part_mask;     // parts per bucket minus one: 7 (an XCD each) or 0
+};
+
+// Appended records: region r holds cap records from r * cap on,
+// counts[r << kCountShift] is the number of appends asked for (it may exceed
+// cap).
+struct Bins {
+  Record *rec;
+  uint32_t *counts;
+  uint32_t cap;
+};
+
+// A record whose bucket is full: OR its missing bits into the filter, one
+// word at a time.  The loads bypass this XCD's caches (agent scope), so that
+// the records of a crowded shard find their bits set instead of issuing
+// atomics.
+__device__ __forceinline__ void apply_direct(Record r, uint64_t *words, BitGeo B) {
+  const int count = (int)(r[2] & 15u) + 1 + B.z;
+  uint64_t *shard = words + ((uint64_t)r[3] << B.sw_log2);
+  const uint32_t groups = (1u << B.sw_log2) / 4u;
+#pragma unroll 1
+  for (uint32_t wd = 0; wd < 4 * groups; ++wd) {
+    uint64_t hi = ((uint64_t)r[0] << 32) | r[1], m = 0;
+    uint32_t lo = r[2];
+#pragma unroll 1
+    for (int j = 0; j < count; ++j) {
+      const uint64_t g = smer_hash(hi >> B.s_shift);
+#pragma unroll 1
+      for (int h = (int)(wd & 3u); h < B.H; h += 4) {
+        const uint32_t a = (uint32_t)(g >> (h * B.slice));
+        if (((a >> 6) & (groups - 1)) == wd >> 2) m |= 1ull << (a & 63u);
+      }
+      hi = (hi << 2) | (lo >> 30);
+      lo <<= 2;
+    }
+    if (m & ~__hip_atomic_load(shard + wd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomic_or64(shard + wd, m);
+  }
+}
+
+// Bit r: bits r .. r+n-1 of x are all set (n >= 1, uniform).
+__device__ __forceinline__ uint64_t window_and_rt(uint64_t x, int n) {
+  for (int have = 1; have < n;) {
+    const int d = have < n - have ? have : n - have;
+    x &= x >> d;
+    have += d;
+  }
+  return x;
+}
+
+// Validity of the lane's 32 k-mers: the 64 bases from granule g0 cover them
+// for k <= 32.
+__device__ __forceinline__ uint32_t kmer_valid32(const uint32_t *s_vb, int g0, int k) {
+  uint64_t vbits = 0, sbits = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t vb = s_vb[g0 + i];
+    vbits |= (uint64_t)(vb & 0xFFFFu) << (16 * i);
+    sbits |= (uint64_t)(vb >> 16) << (16 * i);
+  }
+  uint64_t kv = window_and_rt(vbits, k);
+  // no record starts at r+1 .. r+k-1
+  if (k > 1 && sbits >> 1) kv &= window_and_rt(~(sbits >> 1), k - 1);
+  return (uint32_t)kv;
+}
+
+// Hash of the m-mer at window position j.  MK 0: m = 16; 1: m < 16; 2: m > 16.
+template <int MK>
+__device__ __forceinline__ uint64_t bin_mmer_hash(const uint32_t *a, int j, int m_shift) {
+  if constexpr (MK == 0) return minimizer_hash32_split(win32(a, j));
+  if constexpr (MK == 1) return minimizer_hash32_split(win32(a, j) >> m_shift);
+  return minimizer_hash((((uint64_t)win32(a, j) << 32) | win32(a, j + 16)) >> m_shift);
+}
+
+// stage_granules for the tile of a bin_kernel workgroup: inside an aligned
+// sequence a lane loads all its granules before it encodes the first, and so
+// waits for memory once.
+template <int NGRAN>
+__device__ __forceinline__ void stage_tile(const uint8_t *__restrict__ seq, uint64_t len, uint64_t base,
+                                           const uint32_t *__restrict__ starts, bool aligned16,
+                                           uint32_t *__restrict__ s_codes, uint32_t *__restrict__ s_vb) {
+  constexpr int N = (NGRAN + kBinWG - 1) / kBinWG;
+  if (!aligned16 || base + 16ull * NGRAN > len) {
+    stage_granules<kBinWG>(seq, len, base, starts, aligned16, NGRAN, s_codes, s_vb);
+    return;
+  }
+  u32x4 v[N];
+  uint32_t rs[N];
+  const u32x4 *src = reinterpret_cast<const u32x4 *>(seq + base);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int g = i * kBinWG + threadIdx.x;
+    rs[i] = 0;
+    if (g < NGRAN) {
+      v[i] = __builtin_nontemporal_load(src + g);
+      if (starts != nullptr) rs[i] = (starts[(base >> 5) + (uint32_t)(g >> 1)] >> ((uint32_t)(g & 1) * 16u)) & 0xFFFFu;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int g = i * kBinWG + threadIdx.x;
+    if (g < NGRAN) {
+      uint32_t code = 0, valid = 0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t c8, v4;
+        encode4(v[i][w], c8, v4);
+        code = (code << 8) | c8;
+        valid |= v4 << (4 * w);
+      }
+      s_codes[g] = code;
+      s_vb[g] = valid | (rs[i] << 16);
+    }
+  }
+}
+
+template <int W, int MK, int LCAP>
+__global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) void bin_kernel(
+    const uint8_t *__restrict__ seq, uint64_t len, const uint32_t *__restrict__ starts, int aligned16, BinGeo P,
+    Bins out, uint64_t *__restrict__ words, BitGeo B) {
+  constexpr int L = kBinL;
+  constexpr int NGW = MK == 2 ? 6 : 5;
+  constexpr int NGRAN = (kBinWG - 1) * 2 + NGW;
+  static_assert(LCAP % kBinWG == 0 && LCAP * 16 <= L * kBinWG * 4, "whole records per lane, which fit over the shards");
+  constexpr int RPT = LCAP / kBinWG;
+
+  __shared__ uint32_t s_codes[NGRAN];
+  // validity bits of the staged bases, then the list of record starts
+  __shared__ union {
+    uint32_t vb[NGRAN];
+    uint16_t list[LCAP];
+  } s_u;
+  __shared__ __align__(16) uint32_t s_shard[L][kBinWG];  // then the records in bucket order
+  __shared__ uint32_t s_change[kBinWG];
+  __shared__ uint32_t s_stop[kBinWG + 1];  // validity, then record starts and invalid k-mers
+  __shared__ uint32_t s_hist[1 << kMaxBucketBits1];
+  __shared__ uint32_t s_wsum[kBinWG / 64];
+
+  const int t = threadIdx.x;
+  const uint64_t base = (uint64_t)blockIdx.x * kBinTile;
+  stage_tile<NGRAN>(seq, len, base, starts, aligned16 != 0, s_codes, s_u.vb);
+  for (int b = t; b < P.nbuckets; b += kBinWG) s_hist[b] = 0;
+  __syncthreads();
+
+  const int g0 = t * 2;
+  uint32_t change = 0;  // bit r: k-mer r's shard differs from k-mer r-1's
+  const uint32_t kv = kmer_valid32(s_u.vb, g0, P.k);
+  {
+    uint32_t a[NGW];
+#pragma unroll
+    for (int i = 0; i < NGW; ++i) a[i] = s_codes[g0 + i];
+    uint64_t suf[W];
+    {
+      uint64_t m = bin_mmer_hash<MK>(a, W - 1, P.m_shift);
+      suf[W - 1] = m;
+#pragma unroll
+      for (int i = W - 2; i >= 0; --i) {
+        m = umin64(bin_mmer_hash<MK>(a, i, P.m_shift), m);
+        suf[i] = m;
+      }
+    }
+    uint32_t prev = 0;
+#pragma unroll
+    for (int q = 0; q * W < L; ++q) {
+      uint64_t pre = ~0ull;
+#pragma unroll
+      for (int i = 0; i < W; ++i) {
+        const int r = q * W + i;
+        if (r < L) {
+          uint64_t mu = suf[i];
+          if (i > 0) {
+            const uint64_t h = bin_mmer_hash<MK>(a, r + W - 1, P.m_shift);
+            pre = umin64(pre, h);
+            mu = umin64(mu, pre);
+            suf[i - 1] = h;
+          }
+          const uint32_t sh = (uint32_t)mu & P.shard_mask;
+          s_shard[r][t] = sh;
+          // change = 2 change + (sh != prev)
+          asm("v_cmp_ne_u32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+              : "+v"(change)
+              : "v"(sh), "v"(prev)
+              : "vcc");
+          prev = sh;
+        }
+      }
+      if ((q + 1) * W < L) {
+        uint64_t m = bin_mmer_hash<MK>(a, (q + 1) * W + W - 1, P.m_shift);
+        suf[W - 1] = m;
+#pragma unroll
+        for (int i = W - 2; i >= 0; --i) {
+          m = umin64(suf[i], m);
+          suf[i] = m;
+        }
+      }
+    }
+    change = __builtin_bitreverse32(change);
+  }
+  s_change[t] = change;
+  s_stop[t] = kv;
+  if (t == 0) s_stop[kBinWG] = ~0u;
+  __syncthreads();
+
+  // Record starts among the lane's k-mers: a valid k-mer after an invalid one
+  // or in another shard than the one before; runs of more than nmax k-mers
+  // are cut.
+  uint32_t head;
+  {
+    const uint32_t pkv = t > 0 ? s_stop[t - 1] : 0u;
+    const uint32_t pch = t > 0 ? s_change[t - 1] : 0u;
+    const bool same = t > 0 && (pkv >> 31) && s_shard[L - 1][t > 0 ? t - 1 : 0] == s_shard[0][t];
+    uint32_t fresh = (change & ~1u) | (same ? 0u : 1u);
+    head = kv & (fresh | ~(kv << 1 | (same ? 1u : 0u)));
+    if (same && (kv & 1u)) {
+      // continues the previous lane's last run, of `tail` k-mers there (its
+      // start is not in that lane: taken as too long)
+      const uint32_t phead = pkv & ~1u & (pch | ~(pkv << 1));
+      int tail = phead ? __clz((int)phead) + 1 : 64;
+      while (tail > P.nmax && tail <= 32) tail -= P.nmax;
+      const uint32_t stop = head | ~kv;
+      const int lead = stop ? __ffs((int)stop) - 1 : 32;
+      if (tail + lead > P.nmax) head |= 1u;
+    }
+    for (;;) {
+      // k-mers whose nmax-1 predecessors and themselves continue a run: the
+      // lowest is the run's k-mer number nmax
+      uint32_t c = kv & ~head;
+      for (int have = 1; have < P.nmax;) {
+        const int d = have < P.nmax - have ? have : P.nmax - have;
+        c &= c << d;
+        have += d;
+      }
+      if (c == 0) break;
+      head |= c & (0u - c);
+    }
+  }
+  // positions of the lane's records in the tile's list
+  const int lane = t & 63, wave = t >> 6;
+  const uint32_t mine = (uint32_t)__popc(head);
+  uint32_t incl = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
+  }
+  if (lane == 63) s_wsum[wave] = incl;
+  __syncthreads();
+  s_stop[t] = head | ~kv;
+  uint32_t first = incl - mine, total = 0;
+#pragma unroll
+  for (int w = 0; w < kBinWG / 64; ++w) {
+    if (w < wave) first += s_wsum[w];
+    total += s_wsum[w];
+  }
+  // each XCD appends to its own part of a bucket, so that the part's last
+  // line fills up in that XCD's L2
+  const uint32_t part = blockIdx.x & (uint32_t)P.part_mask, parts = (uint32_t)P.part_mask + 1u;
+
+  // the record of the run from tile position q on
+  auto record = [&](int q) {
+    const int ql = q / L, qr = q & (L - 1);
+    const uint64_t stop = (((uint64_t)s_stop[ql + 1] << 32) | s_stop[ql]) >> (qr + 1);
+    const uint32_t n1 = (uint32_t)__ffs((int)(uint32_t)stop) - 1u;  // k-mers minus one, below 16
+    const uint32_t *a = s_codes + (q >> 4);
+    const int off = (q & 15) * 2;
+    Record rec;
+    rec[0] = (uint32_t)(((((uint64_t)a[0] << 32) | a[1]) << off) >> 32);
+    rec[1] = (uint32_t)(((((uint64_t)a[1] << 32) | a[2]) << off) >> 32);
+    rec[2] = ((uint32_t)(((((uint64_t)a[2] << 32) | a[3]) << off) >> 32) & ~15u) | n1;
+    rec[3] = s_shard[qr][ql];
+    return rec;
+  };
+  auto append = [&](const Record &rec, uint32_t bucket, uint32_t pos) {
+    if (pos < out.cap)
+      out.rec[(uint64_t)(bucket * parts + part) * out.cap + pos] = rec;
+    else
+      apply_direct(rec, words, B);
+  };
+  // list the tile's records from number `done` on
+  auto list = [&](uint32_t done) {
+    uint32_t hm = head, at = first - done;
+    while (hm) {
+      const int r = __ffs((int)hm) - 1;
+      if (at < (uint32_t)LCAP) s_u.list[at] = (uint16_t)(t * L + r);
+      ++at;
+      hm &= hm - 1;
+    }
+  };
+
+  list(0);
+  __syncthreads();
+  if (total <= (uint32_t)LCAP) {
+    // The usual tile: its records are put in bucket order in LDS, over the
+    // shards, so that consecutive lanes append consecutive records.
+    Record rec[RPT];
+    uint32_t rank[RPT];
+#pragma unroll
+    for (int c = 0; c < RPT; ++c) {
+      const uint32_t i = (uint32_t)(c * kBinWG + t);
+      rec[c] = record(s_u.list[i < total ? i : 0]);
+    }
+    // A record equal to the one before it (long homopolymers and the like
+    // are cut into equal records, all for one shard) adds nothing.
+    uint32_t keep = 0;
+#pragma unroll
+    for (int c = 0; c < RPT; ++c) {
+      const bool here = (uint32_t)(c * kBinWG + t) < total;
+      bool same = __shfl_up(rec[c][3], 1, 64) == rec[c][3] && lane > 0 && here;
+      if (__ballot(same)) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) same = (__shfl_up(rec[c][x], 1, 64) == rec[c][x]) && same;
+      }
+      if (here && !same) keep |= 1u << c;
+    }
+#pragma unroll
+    for (int c = 0; c < RPT; ++c)
+      if (keep >> c & 1u) rank[c] = atomicAdd(&s_hist[rec[c][3] >> P.bucket_shift], 1u);
+    __syncthreads();
+    const uint32_t n = t < P.nbuckets ? s_hist[t] : 0u;
+    uint32_t upto = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t o = __shfl_up(upto, d, 64);
+      if (lane >= d) upto += o;
+    }
+    if (lane == 63) s_wsum[wave] = upto;
+    // where the bucket's records go, and (in s_change) where they are in LDS
+    const uint32_t place = n ? atomicAdd(&out.counts[(t * parts + part) << kCountShift], n) : 0u;
+    __syncthreads();
+    uint32_t before = upto - n, kept = 0;
+#pragma unroll
+    for (int w = 0; w < kBinWG / 64; ++w) {
+      if (w < wave) before += s_wsum[w];
+      kept += s_wsum[w];
+    }
+    if (t < P.nbuckets) s_change[t] = before;
+    __syncthreads();
+    Record *sorted = reinterpret_cast<Record *>(&s_shard[0][0]);
+#pragma unroll
+    for (int c = 0; c < RPT; ++c)
+      if (keep >> c & 1u) sorted[s_change[rec[c][3] >> P.bucket_shift] + rank[c]] = rec[c];
+    if (t < P.nbuckets) s_hist[t] = place - before;
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t i = t; i < kept; i += kBinWG) {
+      const Record x = sorted[i];
+      const uint32_t bucket = x[3] >> P.bucket_shift;
+      append(x, bucket, s_hist[bucket] + i);
+    }
+    return;
+  }
+  // more records than the list holds: some at a time, appended as they come
+  for (uint32_t done = 0;;) {
+    const uint32_t here = total - done < (uint32_t)LCAP ? total - done : (uint32_t)LCAP;
+    uint32_t rank[RPT];
+#pragma unroll
+    for (int c = 0; c < RPT; ++c) {
+      const uint32_t i = (uint32_t)(c * kBinWG + t);
+      const int q = s_u.list[i < here ? i : 0];
+      if (i < here) rank[c] = atomicAdd(&s_hist[s_shard[q & (L - 1)][q / L] >> P.bucket_shift], 1u);
+    }
+    __syncthreads();
+    if (t < P.nbuckets) {
+      const uint32_t n = s_hist[t];
+      if (n) s_hist[t] = atomicAdd(&out.counts[(t * parts + part) << kCountShift], n);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < RPT; ++c) {
+      const uint32_t i = (uint32_t)(c * kBinWG + t);
+      if (i < here) {
+        const Record x = record(s_u.list[i]);
+        const uint32_t bucket = x[3] >> P.bucket_shift;
+        append(x, bucket, s_hist[bucket] + rank[c]);
+      }
+    }
+    done += LCAP;
+    if (done >= total) break;
+    __syncthreads();
+    for (int b = t; b < P.nbuckets; b += kBinWG) s_hist[b] = 0;
+    list(done);
+    __syncthreads();
+  }
+}
+
+// Split the records of a group of buckets, from bucket b0 on, into the slices
+// of each.  The tiles of one bucket run on one XCD (workgroups go to the XCDs
+// in turn), so that the records appended to a slice gather in one L2, and a
+// tile's records are put in slice order in LDS first, so that consecutive
+// lanes append consecutive records.
+__global__ __launch_bounds__(kSplitWG) __attribute__((amdgpu_waves_per_eu(4))) void split_kernel(
+    Bins in, Bins out, uint32_t b0, uint32_t tiles_per_region, int slice_shift, uint32_t slices_per_bucket,
+    uint64_t *__restrict__ words, BitGeo B) {
+  __shared__ Record s_rec[kSplitTile];
+  __shared__ uint32_t s_hist[1 << kMaxBucketBits2];   // records per slice, then where they go
+  __shared__ uint16_t s_first[1 << kMaxBucketBits2];  // a slice's first record in s_rec
+  __shared__ uint32_t s_wsum[kSplitWG / 64];
+  const uint32_t per_bucket = tiles_per_region * kXcds;
+  const uint32_t j = blockIdx.x / kXcds;
+  const uint32_t bl = (j / per_bucket) * kXcds + (blockIdx.x & (kXcds - 1));  // bucket - b0
+  const uint32_t region = (b0 + bl) * kXcds + j % kXcds;
+  const uint32_t first = (j % per_bucket) / kXcds * kSplitTile;
+  uint32_t n = in.counts[region << kCountShift];
+  n = n < in.cap ? n : in.cap;
+  if (first >= n) return;
+  n = n - first < (uint32_t)kSplitTile ? n - first : (uint32_t)kSplitTile;
+  const int t = threadIdx.x;
+  for (uint32_t b = t; b < slices_per_bucket; b += kSplitWG) s_hist[b] = 0;
+  const Record *src = in.rec + (uint64_t)region * in.cap + first;
+  const uint32_t sub = slices_per_bucket - 1;
+  Record r[kSplitPer];
+  uint32_t rank[kSplitPer];
+#pragma unroll
+  for (int c = 0; c < kSplitPer; ++c) {
+    const uint32_t i = (uint32_t)(c * kSplitWG + t);
+    r[c] = src[i < n ? i : 0];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < kSplitPer; ++c)
+    if ((uint32_t)(c * kSplitWG + t) < n) rank[c] = atomicAdd(&s_hist[(r[c][3] >> slice_shift) & sub], 1u);
+  __syncthreads();
+  // lane t takes the slices_per_bucket / kSplitWG slices from t times that on
+  constexpr int MAXPER = (1 << kMaxBucketBits2) / kSplitWG;
+  const uint32_t per = slices_per_bucket > (uint32_t)kSplitWG ? slices_per_bucket / kSplitWG : 1u;
+  const uint32_t sb = t * per;
+  uint32_t mine = 0;
+  for (uint32_t x = 0; x < per; ++x)
+    if (sb + x < slices_per_bucket) mine += s_hist[sb + x];
+  uint32_t incl = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if ((t & 63) >= d) incl += o;
+  }
+  if ((t & 63) == 63) s_wsum[t >> 6] = incl;
+  __syncthreads();
+  uint32_t at = incl - mine;
+#pragma unroll
+  for (int w = 0; w < kSplitWG / 64; ++w)
+    if (w < t >> 6) at += s_wsum[w];
+  uint32_t place[MAXPER];
+#pragma unroll
+  for (int x = 0; x < MAXPER; ++x) {
+    if ((uint32_t)x < per && sb + x < slices_per_bucket) {
+      const uint32_t m = s_hist[sb + x];
+      s_first[sb + x] = (uint16_t)at;
+      place[x] = m ? atomicAdd(&out.counts[((uint64_t)(b0 + bl) * slices_per_bucket + sb + x) << kCountShift], m) - at
+                   : 0u;
+      at += m;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < kSplitPer; ++c)
+    if ((uint32_t)(c * kSplitWG + t) < n) s_rec[s_first[(r[c][3] >> slice_shift) & sub] + rank[c]] = r[c];
+#pragma unroll
+  for (int x = 0; x < MAXPER; ++x)
+    if ((uint32_t)x < per && sb + x < slices_per_bucket) s_hist[sb + x] = place[x];
+  __syncthreads();
+#pragma unroll 1
+  for (uint32_t i = t; i < n; i += kSplitWG) {
+    const Record x = s_rec[i];
+    const uint32_t b = (x[3] >> slice_shift) & sub;
+    const uint32_t pos = s_hist[b] + i;
+    if (pos < out.cap)
+      out.rec[((uint64_t)bl * slices_per_bucket + b) * out.cap + pos] = x;
+    else
+      apply_direct(x, words, B);
+  }
+}
+
+// Apply the records of slices s0 .. s0 + nslices - 1, one slice at a time per
+// workgroup.  A slice's records lie in `regions` regions of in, from region
+// (slice - s0) * regions on; counts are indexed from slice 0.  The records are
+// taken in order of length (a counting sort of their indices), so that the
+// lanes of a wave finish together.
+template <int SW, int H, int SB>
+__global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4))) void apply_kernel(
+    Bins in, uint32_t s0, uint32_t nslices, uint32_t regions, uint64_t *__restrict__ words, BitGeo B) {
+  constexpr int SWL = SW == 4 ? 2 : SW == 8 ? 3 : 4;
+  constexpr int WORDS = 1 << SB;                      // 64-bit words of a slice
+  constexpr int WG = 1 << (SB - 4);
+  constexpr int PIECES = WORDS / 2 / WG;  // 16-byte pieces per lane
+  constexpr int SLICE = 64 / H;
+  constexpr int PER = 8;                              // records sorted per lane
+  __shared__ uint64_t s_words[WORDS];
+  __shared__ uint16_t s_list[PER * WG];
+  __shared__ uint32_t s_len[16];
+  const int t = threadIdx.x;
+  acquire_device();
+  uint4 *acc = reinterpret_cast<uint4 *>(s_words);
+  for (uint32_t sl = blockIdx.x; sl < nslices; sl += gridDim.x) {
+    uint4 *line = reinterpret_cast<uint4 *>(words + ((uint64_t)(s0 + sl) << SB));
+    // the slice's words are read now and used only at the end
+    uint4 old[PIECES];
+#pragma unroll
+    for (int c = 0; c < PIECES; ++c) old[c] = line[c * WG + t];
+#pragma unroll
+    for (int c = 0; c < PIECES; ++c) acc[c * WG + t] = make_uint4(0, 0, 0, 0);
+    for (uint32_t g = 0; g < regions; ++g) {
+      uint32_t n = in.counts[((uint64_t)(s0 + sl) * regions + g) << kCountShift];
+      n = n < in.cap ? n : in.cap;
+      const Record *src = in.rec + ((uint64_t)sl * regions + g) * in.cap;
+      for (uint32_t first = 0; first < n; first += PER * WG, src += PER * WG) {
+        const uint32_t here = n - first < PER * WG ? n - first : PER * WG;
+        uint32_t len[PER], rank[PER];
+#pragma unroll
+        for (int c = 0; c < PER; ++c) {
+          const uint32_t i = (uint32_t)(c * WG + t);
+          len[c] = 15u - (reinterpret_cast<const uint32_t *>(src + (i < here ? i : 0))[2] & 15u);
+        }
+        if (t < 16) s_len[t] = 0;
+        __syncthreads();  // also: the previous records are applied, the words are cleared
+#pragma unroll
+        for (int c = 0; c < PER; ++c)
+          if ((uint32_t)(c * WG + t) < here) rank[c] = atomicAdd(&s_len[len[c]], 1u);
+        __syncthreads();
+        if (t < 16) {
+          uint32_t before = 0;
+          for (int j = 0; j < t; ++j) before += s_len[j];
+          __builtin_amdgcn_wave_barrier();
+          s_len[t] = before;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < PER; ++c) {
+          const uint32_t i = (uint32_t)(c * WG + t);
+          if (i < here) s_list[s_len[len[c]] + rank[c]] = (uint16_t)i;
+        }
+        __syncthreads();
+        uint32_t i = t;
+        Record r = src[s_list[i < here ? i : 0] & (PER * WG - 1)];
+        while (i < here) {
+          i += WG;
+          const Record next = src[s_list[i < here ? i : 0]];
+          uint64_t *shard = s_words + ((r[3] & ((WORDS >> SWL) - 1)) << SWL);
+          const int count = (int)(r[2] & 15u) + 1 + B.z;
+          uint32_t x = r[0], y = r[1], w = r[2];
+          uint64_t m[4] = {0, 0, 0, 0};
+#pragma unroll 2
+          for (int j = 0; j < count; ++j) {
+            const uint64_t g = smer_hash((((uint64_t)x << 32) | y) >> B.s_shift);
+            x = __builtin_amdgcn_alignbit(x, y, 30);
+            y = __builtin_amdgcn_alignbit(y, w, 30);
+            w <<= 2;
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+              const uint32_t a = (uint32_t)(g >> (h * SLICE));
+              if constexpr (SW == 4) {
+                m[h & 3] |= 1ull << (a & 63u);
+              } else {
+                atomicOr(
+                    reinterpret_cast<uint32_t *>(shard + (h & 3) + 4 * ((a >> 6) & (SW / 4 - 1))) + ((a >> 5) & 1u),
+                    1u << (a & 31u));
+              }
+            }
+          }
+          if constexpr (SW == 4) {
+#pragma unroll
+            for (int h = 0; h < (H < 4 ? H : 4); ++h)
+              __hip_atomic_fetch_or(shard + h, m[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
+          r = next;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < PIECES; ++c) {
+      const uint4 a = acc[c * WG + t];
+      u32x4 v;
+      v[0] = old[c].x | a.x;
+      v[1] = old[c].y | a.y;
+      v[2] = old[c].z | a.z;
+      v[3] = old[c].w | a.w;
+      *(coherent_u32x4 *)(line + c * WG + t) = v;
+    }
+  }
+}
+
+int log2_of(uint64_t x) {
+  int n = 0;
+  while ((1ull << n) < x) ++n;
+  return n;
+}
+
+uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
+
+// Records of one region holding a share of n expected ones: the spread over
+// buckets of up to 2^11 shares stays within a few percent on genomes; finer
+// shares (slices) spread more.
+uint64_t region_cap(double expected, double slack) {
+  return (uint64_t)std::ceil(expected * slack + 6.0 * std::sqrt(expected) + 64.0);
+}
+
+BitGeo bit_geo(const Geometry &g) {
+  BitGeo B;
+  B.z = (int)(g.k - g.s);
+  B.s_shift = 64 - 2 * (int)g.s;
+  B.H = (int)g.H;
+  B.slice = 64 / (int)g.H;
+  B.sw_log2 = log2_of(g.shard_words);
+  return B;
+}
+
+template <int W, int MK>
+hipError_t launch_bin(const SeqArgs &a, uint64_t nk, const BinGeo &P, const Bins &out, uint64_t *words,
+                      const BitGeo &B, hipStream_t st) {
+  // the list holds a tile's records in one pass at the expected 2 / (w + 1)
+  // per k-mer
+  constexpr int LCAP = W >= 16 && W <= 17 ? 1024 : 2048;
+  const unsigned grid = (unsigned)((nk + kBinTile - 1) / kBinTile);
+  const int aligned = ((uintptr_t)a.seq & 15u) == 0;
+  hipLaunchKernelGGL((bin_kernel<W, MK, LCAP>), dim3(grid), dim3(kBinWG), 0, st, a.seq, a.len, a.starts, aligned, P,
+                     out, words, B);
+  return hipGetLastError();
+}
+
+template <int SW, int SB>
+hipError_t launch_apply_sb(const Bins &in, uint32_t s0, uint32_t nslices, uint32_t regions, uint64_t *words,
+                        const BitGeo &B, hipStream_t st) {
+#define SBF_APPLY(H_)                                                                                        \
+  case H_:                                                                                                   \
+    hipLaunchKernelGGL((apply_kernel<SW, H_, SB>), dim3(std::min(nslices, kApplyGrid << (13 - SB))),          \
+                       dim3(1 << (SB - 4)), 0, st, in, s0, nslices, regions, words, B);                      \
+    break;
+  switch (B.H) {
+    SBF_APPLY(1) SBF_APPLY(2) SBF_APPLY(3) SBF_APPLY(4) SBF_APPLY(5) SBF_APPLY(6) SBF_APPLY(7) SBF_APPLY(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef SBF_APPLY
+  return hipGetLastError();
+}
+
+template <int SW>
+hipError_t launch_apply(int slice_words_log2, const Bins &in, uint32_t s0, uint32_t nslices, uint32_t regions,
+                        uint64_t *words, const BitGeo &B, hipStream_t st) {
+  return slice_words_log2 == 12 ? launch_apply_sb<SW, 12>(in, s0, nslices, regions, words, B, st)
+                                : launch_apply_sb<SW, 13>(in, s0, nslices, regions, words, B, st);
+}
+
+// Compiled (w, m class) pairs: m = 16 at k = 31, and every w = k - m + 1 from
+// 6 on for m <= 16 (MK 1) and m > 16 (MK 2).  Below 6 a batch has a record
+// for every third k-mer or more.
+#define SBF_BIN_SETS(X)                                                                                  \
+  X(16, 0) X(6, 1) X(7, 1) X(8, 1) X(9, 1) X(10, 1) X(11, 1) X(12, 1) X(13, 1) X(14, 1) X(15, 1)          \
+  X(16, 1) X(17, 1) X(18, 1) X(19, 1) X(20, 1) X(21, 1) X(22, 1) X(23, 1) X(24, 1) X(25, 1) X(26, 1)      \
+  X(27, 1) X(28, 1) X(29, 1) X(30, 1) X(31, 1) X(32, 1) X(6, 2) X(7, 2) X(8, 2) X(9, 2) X(10, 2) X(11, 2) \
+  X(12, 2) X(13, 2) X(14, 2) X(15, 2) X(16, 2)
+
+bool bin_compiled(int w, int mk) {
+#define SBF_MATCH(W_, MK_) \
+  if (w == W_ && mk == MK_) return true;
+  SBF_BIN_SETS(SBF_MATCH)
+#undef SBF_MATCH
+  return false;
+}
+
+int mk_of(uint32_t k, uint32_t m) { return m > 16 ? 2 : k == 31 && m == 16 ? 0 : 1; }
+
+// k-mers of a record: 16, fewer where their bases would reach the low 4 bits
+int record_kmers(uint32_t k) { return std::min(16, 47 - (int)k); }
+
+}  // namespace
+
+bool binned_plan(const Geometry &g, uint64_t len, bool lane_family, BinPlan &p) {
+  if (len < g.k || g.k > 32 || g.H > 8 || g.nshards > (1ull << 32)) return false;
+  const int w = (int)(g.k - g.m + 1);
+  if (!bin_compiled(w, mk_of(g.k, g.m))) return false;
+  const uint64_t nk = len - g.k + 1;
+  const int words_bits = log2_of(g.nshards) + log2_of(g.shard_words);
+  const uint64_t nbits = 64ull << words_bits;
+  if (nk < kMinBinnedKmers) return false;
+  if (nbits > (lane_family ? kLaneSmallBits : kOtherSmallBits) &&
+      nk < nbits / (lane_family ? kLaneBitsPerKmer : kOtherBitsPerKmer))
+    return false;
+  // 32 KB slices give the apply pass four independent workgroups per CU
+  // (7% faster than two of 64 KB on a 256 MiB filter); beyond 2^14 slices the
+  // split pass loses more with twice the slices.
+  p.slice_words_log2 = words_bits - 12 <= 14 ? 12 : 13;
+  p.slice_shift = p.slice_words_log2 - log2_of(g.shard_words);
+  const int slice_bits = words_bits - p.slice_words_log2;
+  if (slice_bits < kMinSliceBits || slice_bits > kMaxBucketBits1 + kMaxBucketBits2) return false;
+  p.bits1 = slice_bits <= kMaxBucketBits1 ? slice_bits : std::min(kMaxBucketBits1, (slice_bits + 1) / 2);
+  p.bits2 = slice_bits - p.bits1;
+  p.chunk = std::min(nk, std::max(nbits / 15, kMinChunkKmers));
+  p.chunk = (p.chunk + kBinTile - 1) / kBinTile * kBinTile;
+  // a small batch does not fill eight parts of each bucket
+  p.parts = p.bits2 == 0 && p.chunk <= kOnePartKmers ? 1 : kXcds;
+  const int nmax = record_kmers(g.k);
+  double density = 2.0 / (w + 1) + 1.0 / kBinTile;
+  if (w > nmax) density *= 1.0 + (double)(w - nmax) / w;
+  const double records = density * (double)p.chunk;
+  const uint64_t buckets = 1ull << p.bits1, slices = 1ull << slice_bits;
+  p.cap1 = region_cap(records / (double)(buckets * p.parts), 1.12);
+  p.cap2 = 0;
+  p.counts1 = 0;
+  uint64_t bytes = align256((buckets * p.parts * 4) << kCountShift);
+  p.counts2 = bytes;
+  p.group = (uint32_t)buckets;
+  if (p.bits2) {
+    bytes += align256((slices * 4) << kCountShift);
+    p.cap2 = region_cap(records / (double)slices, 1.4);
+    // buckets split and applied together: at most 1 GiB of records
+    const uint64_t per_bucket = (p.cap2 << p.bits2) * sizeof(Record);
+    while (p.group > (uint32_t)kXcds && p.group * per_bucket > (1ull << 30)) p.group /= 2;
+  }
+  p.count_words = bytes / 4;
+  p.rec1 = bytes;
+  bytes += align256(buckets * p.parts * p.cap1 * sizeof(Record));
+  p.rec2 = bytes;
+  if (p.bits2) bytes += align256(((uint64_t)p.group << p.bits2) * p.cap2 * sizeof(Record));
+  p.bytes = bytes;
+  return p.cap1 < (1ull << 31) && p.cap2 < (1ull << 31);
+}
+
+hipError_t launch_insert_binned(const Geometry &g, uint64_t *words, const SeqArgs &a, const BinPlan &p, void *scratch,
+                                hipStream_t st) {
+  uint8_t *s = (uint8_t *)scratch;
+  const BitGeo B = bit_geo(g);
+  const int mk = mk_of(g.k, g.m), w = (int)(g.k - g.m + 1);
+  BinGeo P;
+  P.k = (int)g.k;
+  P.m_shift = mk == 2 ? 64 - 2 * (int)g.m : 32 - 2 * (int)g.m;
+  P.nmax = record_kmers(g.k);
+  P.shard_mask = (uint32_t)(g.nshards - 1);
+  P.bucket_shift = p.slice_shift + p.bits2;
+  P.nbuckets = 1 << p.bits1;
+  P.part_mask = (int)p.parts - 1;
+  const Bins b1{(Record *)(s + p.rec1), (uint32_t *)(s + p.counts1), (uint32_t)p.cap1};
+  const Bins b2{(Record *)(s + p.rec2), (uint32_t *)(s + p.counts2), (uint32_t)p.cap2};
+  const uint64_t nk_all = a.len - g.k + 1;
+  for (uint64_t c0 = 0; c0 < nk_all; c0 += p.chunk) {
+    // chunks start at whole tiles, so the sequence stays 16-byte aligned and
+    // the record-start bits start at a word
+    const uint64_t nk = std::min(p.chunk, nk_all - c0);
+    SeqArgs c = a;
+    c.seq = a.seq + c0;
+    c.len = nk + g.k - 1;
+    c.starts = a.starts ? a.starts + c0 / 32 : nullptr;
+    hipError_t e = launch_fill_u32((uint32_t *)(s + p.counts1), p.count_words, 0u, st);
+    if (e != hipSuccess) return e;
+    e = hipErrorInvalidValue;
+#define SBF_CALL(W_, MK_) \
+  if (w == W_ && mk == MK_) e = launch_bin<W_, MK_>(c, nk, P, b1, words, B, st);
+    SBF_BIN_SETS(SBF_CALL)
+#undef SBF_CALL
+    if (e != hipSuccess) return e;
+    const uint32_t buckets = 1u << p.bits1;
+    for (uint32_t b0 = 0; b0 < buckets; b0 += p.group) {
+      Bins in = b1;
+      uint32_t s0 = b0, nslices = buckets, regions = p.parts;
+      if (p.bits2) {
+        const uint32_t tiles = ((uint32_t)p.cap1 + kSplitTile - 1) / kSplitTile;
+        hipLaunchKernelGGL(split_kernel, dim3(p.group * kXcds * tiles), dim3(kSplitWG), 0, st, b1, b2, b0, tiles,
+                           p.slice_shift, 1u << p.bits2, words, B);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        in = b2;
+        s0 = b0 << p.bits2;
+        nslices = p.group << p.bits2;
+        regions = 1;
+      }
+      switch (g.shard_words) {
+        case 4: e = launch_apply<4>(p.slice_words_log2, in, s0, nslices, regions, words, B, st); break;
+        case 8: e = launch_apply<8>(p.slice_words_log2, in, s0, nslices, regions, words, B, st); break;
+        default: e = launch_apply<16>(p.slice_words_log2, in, s0, nslices, regions, words, B, st); break;
+      }
+      if (e != hipSuccess) return e;
+    }
+  }
+  return hipSuccess;
+}
+
+}  // namespace sbf

@@ -122,6 +122,8 @@ struct sbf_filter {
   std::unordered_map<hipStream_t, Scratch> starts;
   // work-queue counters of persistent launches, one set per stream
   std::unordered_map<hipStream_t, Scratch> queues;
+  // records of binned inserts (inserts into one filter never overlap)
+  Scratch bins;
 };
 
 namespace {
@@ -247,9 +249,57 @@ void sbf::release_stream(sbf_filter *f, hipStream_t st) {
 
 namespace {
 
-int run_insert(sbf_filter *f, const SeqArgs &a, hipStream_t st, const sbf::LaunchShape *given = nullptr) {
+// True when an insert of len bases takes the binned kernels: the two-pass
+// strategy at the family's default tile.
+bool binned(const sbf_filter *f, uint64_t len, sbf::BinPlan &plan) {
+  const Family fam = family(f);
+  return f->insert_mode == SBF_INSERT_TWO_PASS && f->insert_lane_len == 0 && fam != kGenericFamily &&
+         sbf::binned_plan(f->g, len, fam == kLaneFamily, plan);
+}
+
+// Grow the record scratch s of binned inserts to plan.bytes.  False without
+// the memory (the insert then takes the two passes); the program keeps at
+// least as much free memory as the records take.
+bool grow_bins(Scratch &s, const sbf::BinPlan &plan) {
+  if (s.bytes >= plan.bytes) return true;
+  if (s.ptr) {
+    // the old buffer may be in use by earlier inserts, on any stream
+    if (hipDeviceSynchronize() != hipSuccess) return false;
+    (void)hipFree(s.ptr);
+    s = Scratch();
+  }
+  size_t free_bytes = 0, total_bytes = 0;
+  if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || plan.bytes > free_bytes / 2 ||
+      grow(s, plan.bytes, "insert records") != SBF_OK) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return true;
+}
+
+// The filter's own record scratch for a binned insert on st; not under stream
+// capture, which may not allocate and whose graph would keep the address.
+bool filter_bins(sbf_filter *f, const sbf::BinPlan &plan, hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return grow_bins(f->bins, plan);
+}
+
+// `given` and `bins`: a graph's own launch counters and record scratch (bins
+// may be null: two passes).
+int run_insert(sbf_filter *f, const SeqArgs &a, hipStream_t st, const sbf::LaunchShape *given = nullptr,
+               const Scratch *bins = nullptr) {
   const int mode = f->insert_mode == SBF_INSERT_ATOMIC ? sbf::kInsertAtomicMode : sbf::kInsertTwoPassMode;
   hipError_t e;
+  sbf::BinPlan plan;
+  if (binned(f, a.len, plan) && (given ? bins && bins->bytes >= plan.bytes : filter_bins(f, plan, st))) {
+    e = sbf::launch_insert_binned(f->g, f->words, a, plan, given ? bins->ptr : f->bins.ptr, st);
+    if (e != hipSuccess) return hip_error(e, "insert kernel launch");
+    return SBF_OK;
+  }
   if (use_rolling(f)) {
     sbf::LaunchShape ls;
     if (given) {
@@ -699,6 +749,7 @@ void sbf_destroy(sbf_filter *f) {
     if (kv.second.ptr) (void)hipFree(kv.second.ptr);
   for (auto &kv : f->queues)
     if (kv.second.ptr) (void)hipFree(kv.second.ptr);
+  if (f->bins.ptr) (void)hipFree(f->bins.ptr);
   for (PipeSlot &ps : f->pipe) {
     for (Scratch *d : {&ps.d_seq, &ps.d_out, &ps.d_off})
       if (d->ptr) (void)hipFree(d->ptr);
@@ -1049,7 +1100,7 @@ struct sbf_graph {
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  Scratch starts_ins, starts_q, queue;
+  Scratch starts_ins, starts_q, queue, bins;
 };
 
 namespace {
@@ -1068,6 +1119,7 @@ void graph_release(sbf_graph *g) {
   free_scratch(g->starts_ins);
   free_scratch(g->starts_q);
   free_scratch(g->queue);
+  free_scratch(g->bins);
   delete g;
 }
 
@@ -1116,6 +1168,8 @@ sbf_graph *sbf_graph_create(sbf_filter *f, int clear_first, const char *d_ins, u
   int rc = grow(g->queue, 256, "work-queue counters");
   if (!rc && do_ins && ins_nrec > 1) rc = grow(g->starts_ins, (ins_len + 31) / 32 * 4, "record-start bits");
   if (!rc && do_q && q_nrec > 1) rc = grow(g->starts_q, (q_len + 31) / 32 * 4, "record-start bits");
+  sbf::BinPlan plan;
+  if (!rc && do_ins && binned(f, ins_len, plan)) (void)grow_bins(g->bins, plan);
   hipError_t e = hipSuccess;
   if (!rc) {
     e = hipStreamCreateWithFlags(&g->cap, hipStreamNonBlocking);
@@ -1141,7 +1195,7 @@ sbf_graph *sbf_graph_create(sbf_filter *f, int clear_first, const char *d_ins, u
   if (!rc && do_q) rc = mark_into(g->starts_q, d_q_off, q_nrec, q_len, g->cap, &st_q);
   if (!rc && do_ins) {
     SeqArgs a{(const uint8_t *)d_ins, ins_len, st_ins, nullptr, 0};
-    rc = run_insert(f, a, g->cap, &ls);
+    rc = run_insert(f, a, g->cap, &ls, &g->bins);
   }
   if (!rc && do_q) {
     SeqArgs a{(const uint8_t *)d_q, q_len, st_q, d_out, q_len};
@@ -1257,6 +1311,7 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
     return SBF_OK;
   };
   float best_ins = 1e30f, best_q = 1e30f;
+  bool best_binned = false;
   int bi_mode = f->insert_mode, bq_mode = f->query_mode;
   uint32_t bi_shape = f->insert_wgs_per_cu, bq_shape = f->query_wgs_per_cu, bi_len = 0, bq_len = 0;
   const Family fam = family(f);
@@ -1280,6 +1335,18 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
     if (q_lens.empty()) q_lens.push_back(0);
     // the insert's repair walk runs at the query's default lane length here
     t->query_lane_len = 0;
+    // the default of a large batch, where the compiled tile does not matter
+    t->insert_mode = SBF_INSERT_TWO_PASS;
+    t->insert_lane_len = 0;
+    sbf::BinPlan plan;
+    if (!rc && binned(t, ins.len, plan)) {
+      rc = time_it(true, best_ins);
+      if (!rc) {
+        line("insert binned: %.4f ms\n", best_ins);
+        bi_mode = SBF_INSERT_TWO_PASS;
+        best_binned = true;
+      }
+    }
     for (int mode : {SBF_INSERT_TWO_PASS, SBF_INSERT_ATOMIC}) {
       for (uint32_t len : ins_lens) {
         for (uint32_t sh : shapes) {
@@ -1298,6 +1365,7 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
             bi_mode = mode;
             bi_shape = sh;
             bi_len = len;
+            best_binned = false;
           }
         }
       }
@@ -1331,9 +1399,12 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
       }
     }
     if (!rc) {
-      line("best insert: %s, %u k-mers/lane, workgroups/CU %u (%.4f ms)\n",
-           bi_mode == SBF_INSERT_ATOMIC ? "atomic" : "two-pass", lane_len_effective(f, bi_len, true), bi_shape,
-           best_ins);
+      if (best_binned)
+        line("best insert: binned (%.4f ms)\n", best_ins);
+      else
+        line("best insert: %s, %u k-mers/lane, workgroups/CU %u (%.4f ms)\n",
+             bi_mode == SBF_INSERT_ATOMIC ? "atomic" : "two-pass", lane_len_effective(f, bi_len, true), bi_shape,
+             best_ins);
       line("best query: %s, %u k-mers/lane, workgroups/CU %u (%.4f ms)\n",
            wide ? wide_name : bq_mode == SBF_QUERY_LANE ? "lane" : bq_mode == SBF_QUERY_LEADER ? "leader" : "direct",
            bq_mode == SBF_QUERY_LANE ? lane_len_effective(f, bq_len, false) : 16u, bq_shape, best_q);
@@ -1473,7 +1544,8 @@ int sbf_autotune_geometry(uint32_t k, uint32_t s, uint32_t m, uint32_t H, uint64
     if (!rc) rc = fill_filter(f, ins);
     if (!rc) rc = count_present(f, neg, &present);
     uint32_t il = 0, ql = 0;
-    if (!rc) rc = sbf_get_tile(f, &il, &ql);
+    if (!rc) rc = sbf_get_tile(f, nullptr, &ql);
+    il = f->insert_lane_len;  // 0: the default, which may be the binned insert
     const int fam = sbf_get_variant(f);
     sbf_destroy(f);
     if (rc) break;

@@ -77,6 +77,25 @@ hipError_t launch_insert_param(const Geometry &g, uint64_t *words, const SeqArgs
                                hipStream_t st);
 hipError_t launch_query_param(const Geometry &g, const uint64_t *words, const SeqArgs &a, const LaunchShape &ls,
                               hipStream_t st);
+// Binned insert (kernels_binned.hip): large batches against any shard size
+// with H <= 8.  binned_plan says whether a batch of len bases takes it instead
+// of the two-pass insert of the lane or another family, and lays out its
+// scratch (p.bytes of device memory).
+struct BinPlan {
+  int slice_words_log2;   // 64-bit words per slice
+  int slice_shift;        // log2 shards per slice
+  int bits1, bits2;       // log2 buckets, log2 slices per bucket
+  uint32_t parts;         // parts per bucket
+  uint32_t group;         // buckets split and applied together
+  uint64_t chunk;         // k-mers binned at a time
+  uint64_t cap1, cap2;    // records per region
+  uint64_t counts1, counts2, rec1, rec2;  // byte offsets in the scratch
+  uint64_t count_words;   // 32-bit counters from counts1 on
+  uint64_t bytes;
+};
+bool binned_plan(const Geometry &g, uint64_t len, bool lane_family, BinPlan &p);
+hipError_t launch_insert_binned(const Geometry &g, uint64_t *words, const SeqArgs &a, const BinPlan &p, void *scratch,
+                                hipStream_t st);
 hipError_t launch_insert_generic(const Geometry &g, uint64_t *words, const SeqArgs &a, hipStream_t st);
 hipError_t launch_query_generic(const Geometry &g, const uint64_t *words, const SeqArgs &a, hipStream_t st);
 
