@@ -11,7 +11,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsbf.so")
 SOURCES = ["sbf_api.hip", "sbf_server.hip", "kernels_rolling.hip", "kernels_wide.hip", "kernels_param.hip",
-           "kernels_generic.hip", "kernels_binned.hip"]
+           "kernels_generic.hip", "kernels_binned.hip", "kernels_runs4.hip",
+           "kernels_runs8.hip", "kernels_runs16.hip"]
 PROBE_LIB = os.path.join(PKG, "libsbf_probe.so")
 PROBE_SOURCES = ["probe_random_access.hip"]
 

@@ -18,9 +18,7 @@
 // another and no repair pass is needed.  A record that finds its bucket full
 // (a batch far from the expected spread over shards) is applied at once with
 // atomic ORs of the bits that are missing, before any slice is read.
-#include "sbf_device.h"
-#include "sbf_internal.h"
-#include "sbf_tiles.h"
+#include "sbf_runs.h"
 
 #include <algorithm>
 #include <cmath>
@@ -29,8 +27,7 @@ namespace sbf {
 namespace {
 
 constexpr int kBinWG = 256;
-constexpr int kBinL = 32;                   // k-mers per lane
-constexpr int kBinTile = kBinWG * kBinL;    // k-mers per tile
+constexpr int kBinTile = kBinWG * kRunL;    // k-mers per tile
 constexpr int kCountShift = 5;              // counters one 128-byte line apart
 constexpr int kXcds = 8;
 constexpr int kMaxBucketBits1 = 8;
@@ -71,20 +68,7 @@ constexpr uint64_t kLaneBitsPerKmer = 112, kOtherBitsPerKmer = 256;
 // its shard in w.
 typedef u32x4 Record;
 
-// Run-time geometry of the records' bits.
-struct BitGeo {
-  int z;        // k - s
-  int s_shift;  // 64 - 2s
-  int H;
-  int slice;    // 64 / H
-  int sw_log2;  // log2 of the words per shard
-};
-
 struct BinGeo {
-  int k;
-  int m_shift;  // 32 - 2m for m <= 16, 64 - 2m above
-  int nmax;     // k-mers per record
-  uint32_t shard_mask;
   int bucket_shift;  // shard >> bucket_shift = bucket
   int nbuckets;
   int part_mask;     // parts per bucket minus one: 7 (an XCD each) or 0
@@ -126,236 +110,37 @@ __device__ __forceinline__ void apply_direct(Record r, uint64_t *words, BitGeo B
   }
 }
 
-// Bit r: bits r .. r+n-1 of x are all set (n >= 1, uniform).
-__device__ __forceinline__ uint64_t window_and_rt(uint64_t x, int n) {
-  for (int have = 1; have < n;) {
-    const int d = have < n - have ? have : n - have;
-    x &= x >> d;
-    have += d;
-  }
-  return x;
-}
-
-// Validity of the lane's 32 k-mers: the 64 bases from granule g0 cover them
-// for k <= 32.
-__device__ __forceinline__ uint32_t kmer_valid32(const uint32_t *s_vb, int g0, int k) {
-  uint64_t vbits = 0, sbits = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t vb = s_vb[g0 + i];
-    vbits |= (uint64_t)(vb & 0xFFFFu) << (16 * i);
-    sbits |= (uint64_t)(vb >> 16) << (16 * i);
-  }
-  uint64_t kv = window_and_rt(vbits, k);
-  // no record starts at r+1 .. r+k-1
-  if (k > 1 && sbits >> 1) kv &= window_and_rt(~(sbits >> 1), k - 1);
-  return (uint32_t)kv;
-}
-
-// Hash of the m-mer at window position j.  MK 0: m = 16; 1: m < 16; 2: m > 16.
-template <int MK>
-__device__ __forceinline__ uint64_t bin_mmer_hash(const uint32_t *a, int j, int m_shift) {
-  if constexpr (MK == 0) return minimizer_hash32_split(win32(a, j));
-  if constexpr (MK == 1) return minimizer_hash32_split(win32(a, j) >> m_shift);
-  return minimizer_hash((((uint64_t)win32(a, j) << 32) | win32(a, j + 16)) >> m_shift);
-}
-
-// stage_granules for the tile of a bin_kernel workgroup: inside an aligned
-// sequence a lane loads all its granules before it encodes the first, and so
-// waits for memory once.
-template <int NGRAN>
-__device__ __forceinline__ void stage_tile(const uint8_t *__restrict__ seq, uint64_t len, uint64_t base,
-                                           const uint32_t *__restrict__ starts, bool aligned16,
-                                           uint32_t *__restrict__ s_codes, uint32_t *__restrict__ s_vb) {
-  constexpr int N = (NGRAN + kBinWG - 1) / kBinWG;
-  if (!aligned16 || base + 16ull * NGRAN > len) {
-    stage_granules<kBinWG>(seq, len, base, starts, aligned16, NGRAN, s_codes, s_vb);
-    return;
-  }
-  u32x4 v[N];
-  uint32_t rs[N];
-  const u32x4 *src = reinterpret_cast<const u32x4 *>(seq + base);
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int g = i * kBinWG + threadIdx.x;
-    rs[i] = 0;
-    if (g < NGRAN) {
-      v[i] = __builtin_nontemporal_load(src + g);
-      if (starts != nullptr) rs[i] = (starts[(base >> 5) + (uint32_t)(g >> 1)] >> ((uint32_t)(g & 1) * 16u)) & 0xFFFFu;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int g = i * kBinWG + threadIdx.x;
-    if (g < NGRAN) {
-      uint32_t code = 0, valid = 0;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        uint32_t c8, v4;
-        encode4(v[i][w], c8, v4);
-        code = (code << 8) | c8;
-        valid |= v4 << (4 * w);
-      }
-      s_codes[g] = code;
-      s_vb[g] = valid | (rs[i] << 16);
-    }
-  }
-}
-
-template <int W, int MK, int LCAP>
+template <int W, int MK>
 __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) void bin_kernel(
-    const uint8_t *__restrict__ seq, uint64_t len, const uint32_t *__restrict__ starts, int aligned16, BinGeo P,
-    Bins out, uint64_t *__restrict__ words, BitGeo B) {
-  constexpr int L = kBinL;
-  constexpr int NGW = MK == 2 ? 6 : 5;
-  constexpr int NGRAN = (kBinWG - 1) * 2 + NGW;
-  static_assert(LCAP % kBinWG == 0 && LCAP * 16 <= L * kBinWG * 4, "whole records per lane, which fit over the shards");
+    const uint8_t *__restrict__ seq, uint64_t len, const uint32_t *__restrict__ starts, int aligned16, RunGeo P,
+    BinGeo G, Bins out, uint64_t *__restrict__ words, BitGeo B) {
+  constexpr int LCAP = run_list_cap<W, kBinWG>();
+  using Tile = RunTile<kBinWG, LCAP>;
+  static_assert(LCAP % kBinWG == 0 && LCAP * 16 <= kRunL * kBinWG * 4, "whole records per lane, which fit over the shards");
   constexpr int RPT = LCAP / kBinWG;
-
-  __shared__ uint32_t s_codes[NGRAN];
-  // validity bits of the staged bases, then the list of record starts
-  __shared__ union {
-    uint32_t vb[NGRAN];
-    uint16_t list[LCAP];
-  } s_u;
-  __shared__ __align__(16) uint32_t s_shard[L][kBinWG];  // then the records in bucket order
-  __shared__ uint32_t s_change[kBinWG];
-  __shared__ uint32_t s_stop[kBinWG + 1];  // validity, then record starts and invalid k-mers
-  __shared__ uint32_t s_hist[1 << kMaxBucketBits1];
-  __shared__ uint32_t s_wsum[kBinWG / 64];
+  __shared__ Tile T;
+  __shared__ uint16_t s_before[1 << kMaxBucketBits1];  // a bucket's first record in the sorted tile
+  static_assert((1 << kMaxBucketBits1) <= kBinWG, "a bucket per lane");
 
   const int t = threadIdx.x;
-  const uint64_t base = (uint64_t)blockIdx.x * kBinTile;
-  stage_tile<NGRAN>(seq, len, base, starts, aligned16 != 0, s_codes, s_u.vb);
-  for (int b = t; b < P.nbuckets; b += kBinWG) s_hist[b] = 0;
-  __syncthreads();
-
-  const int g0 = t * 2;
-  uint32_t change = 0;  // bit r: k-mer r's shard differs from k-mer r-1's
-  const uint32_t kv = kmer_valid32(s_u.vb, g0, P.k);
-  {
-    uint32_t a[NGW];
-#pragma unroll
-    for (int i = 0; i < NGW; ++i) a[i] = s_codes[g0 + i];
-    uint64_t suf[W];
-    {
-      uint64_t m = bin_mmer_hash<MK>(a, W - 1, P.m_shift);
-      suf[W - 1] = m;
-#pragma unroll
-      for (int i = W - 2; i >= 0; --i) {
-        m = umin64(bin_mmer_hash<MK>(a, i, P.m_shift), m);
-        suf[i] = m;
-      }
-    }
-    uint32_t prev = 0;
-#pragma unroll
-    for (int q = 0; q * W < L; ++q) {
-      uint64_t pre = ~0ull;
-#pragma unroll
-      for (int i = 0; i < W; ++i) {
-        const int r = q * W + i;
-        if (r < L) {
-          uint64_t mu = suf[i];
-          if (i > 0) {
-            const uint64_t h = bin_mmer_hash<MK>(a, r + W - 1, P.m_shift);
-            pre = umin64(pre, h);
-            mu = umin64(mu, pre);
-            suf[i - 1] = h;
-          }
-          const uint32_t sh = (uint32_t)mu & P.shard_mask;
-          s_shard[r][t] = sh;
-          // change = 2 change + (sh != prev)
-          asm("v_cmp_ne_u32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-              : "+v"(change)
-              : "v"(sh), "v"(prev)
-              : "vcc");
-          prev = sh;
-        }
-      }
-      if ((q + 1) * W < L) {
-        uint64_t m = bin_mmer_hash<MK>(a, (q + 1) * W + W - 1, P.m_shift);
-        suf[W - 1] = m;
-#pragma unroll
-        for (int i = W - 2; i >= 0; --i) {
-          m = umin64(suf[i], m);
-          suf[i] = m;
-        }
-      }
-    }
-    change = __builtin_bitreverse32(change);
-  }
-  s_change[t] = change;
-  s_stop[t] = kv;
-  if (t == 0) s_stop[kBinWG] = ~0u;
-  __syncthreads();
-
-  // Record starts among the lane's k-mers: a valid k-mer after an invalid one
-  // or in another shard than the one before; runs of more than nmax k-mers
-  // are cut.
-  uint32_t head;
-  {
-    const uint32_t pkv = t > 0 ? s_stop[t - 1] : 0u;
-    const uint32_t pch = t > 0 ? s_change[t - 1] : 0u;
-    const bool same = t > 0 && (pkv >> 31) && s_shard[L - 1][t > 0 ? t - 1 : 0] == s_shard[0][t];
-    uint32_t fresh = (change & ~1u) | (same ? 0u : 1u);
-    head = kv & (fresh | ~(kv << 1 | (same ? 1u : 0u)));
-    if (same && (kv & 1u)) {
-      // continues the previous lane's last run, of `tail` k-mers there (its
-      // start is not in that lane: taken as too long)
-      const uint32_t phead = pkv & ~1u & (pch | ~(pkv << 1));
-      int tail = phead ? __clz((int)phead) + 1 : 64;
-      while (tail > P.nmax && tail <= 32) tail -= P.nmax;
-      const uint32_t stop = head | ~kv;
-      const int lead = stop ? __ffs((int)stop) - 1 : 32;
-      if (tail + lead > P.nmax) head |= 1u;
-    }
-    for (;;) {
-      // k-mers whose nmax-1 predecessors and themselves continue a run: the
-      // lowest is the run's k-mer number nmax
-      uint32_t c = kv & ~head;
-      for (int have = 1; have < P.nmax;) {
-        const int d = have < P.nmax - have ? have : P.nmax - have;
-        c &= c << d;
-        have += d;
-      }
-      if (c == 0) break;
-      head |= c & (0u - c);
-    }
-  }
-  // positions of the lane's records in the tile's list
   const int lane = t & 63, wave = t >> 6;
-  const uint32_t mine = (uint32_t)__popc(head);
-  uint32_t incl = mine;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t o = __shfl_up(incl, d, 64);
-    if (lane >= d) incl += o;
-  }
-  if (lane == 63) s_wsum[wave] = incl;
-  __syncthreads();
-  s_stop[t] = head | ~kv;
-  uint32_t first = incl - mine, total = 0;
-#pragma unroll
-  for (int w = 0; w < kBinWG / 64; ++w) {
-    if (w < wave) first += s_wsum[w];
-    total += s_wsum[w];
-  }
+  uint32_t head, first, total;
+  find_runs<W, MK>(T, seq, len, (uint64_t)blockIdx.x * kBinTile, starts, aligned16 != 0, P, head, first, total);
+  uint32_t *s_hist = T.change;  // records per bucket, then where they go
+  s_hist[t] = 0;
   // each XCD appends to its own part of a bucket, so that the part's last
   // line fills up in that XCD's L2
-  const uint32_t part = blockIdx.x & (uint32_t)P.part_mask, parts = (uint32_t)P.part_mask + 1u;
+  const uint32_t part = blockIdx.x & (uint32_t)G.part_mask, parts = (uint32_t)G.part_mask + 1u;
 
   // the record of the run from tile position q on
   auto record = [&](int q) {
-    const int ql = q / L, qr = q & (L - 1);
-    const uint64_t stop = (((uint64_t)s_stop[ql + 1] << 32) | s_stop[ql]) >> (qr + 1);
-    const uint32_t n1 = (uint32_t)__ffs((int)(uint32_t)stop) - 1u;  // k-mers minus one, below 16
-    const uint32_t *a = s_codes + (q >> 4);
-    const int off = (q & 15) * 2;
+    uint32_t x, y, z;
+    run_bases(T, q, x, y, z);
     Record rec;
-    rec[0] = (uint32_t)(((((uint64_t)a[0] << 32) | a[1]) << off) >> 32);
-    rec[1] = (uint32_t)(((((uint64_t)a[1] << 32) | a[2]) << off) >> 32);
-    rec[2] = ((uint32_t)(((((uint64_t)a[2] << 32) | a[3]) << off) >> 32) & ~15u) | n1;
-    rec[3] = s_shard[qr][ql];
+    rec[0] = x;
+    rec[1] = y;
+    rec[2] = (z & ~15u) | run_length1(T, q);
+    rec[3] = T.shard[q & (kRunL - 1)][q / kRunL] & P.shard_mask;
     return rec;
   };
   auto append = [&](const Record &rec, uint32_t bucket, uint32_t pos) {
@@ -364,18 +149,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     else
       apply_direct(rec, words, B);
   };
-  // list the tile's records from number `done` on
-  auto list = [&](uint32_t done) {
-    uint32_t hm = head, at = first - done;
-    while (hm) {
-      const int r = __ffs((int)hm) - 1;
-      if (at < (uint32_t)LCAP) s_u.list[at] = (uint16_t)(t * L + r);
-      ++at;
-      hm &= hm - 1;
-    }
-  };
-
-  list(0);
+  list_runs(T, head, first, 0);
   __syncthreads();
   if (total <= (uint32_t)LCAP) {
     // The usual tile: its records are put in bucket order in LDS, over the
@@ -385,7 +159,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
     for (int c = 0; c < RPT; ++c) {
       const uint32_t i = (uint32_t)(c * kBinWG + t);
-      rec[c] = record(s_u.list[i < total ? i : 0]);
+      rec[c] = record(T.list[i < total ? i : 0]);
     }
     // A record equal to the one before it (long homopolymers and the like
     // are cut into equal records, all for one shard) adds nothing.
@@ -402,37 +176,37 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
 #pragma unroll
     for (int c = 0; c < RPT; ++c)
-      if (keep >> c & 1u) rank[c] = atomicAdd(&s_hist[rec[c][3] >> P.bucket_shift], 1u);
+      if (keep >> c & 1u) rank[c] = atomicAdd(&s_hist[rec[c][3] >> G.bucket_shift], 1u);
     __syncthreads();
-    const uint32_t n = t < P.nbuckets ? s_hist[t] : 0u;
+    const uint32_t n = t < G.nbuckets ? s_hist[t] : 0u;
     uint32_t upto = n;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
       const uint32_t o = __shfl_up(upto, d, 64);
       if (lane >= d) upto += o;
     }
-    if (lane == 63) s_wsum[wave] = upto;
-    // where the bucket's records go, and (in s_change) where they are in LDS
+    if (lane == 63) T.wsum[wave] = upto;
+    // where the bucket's records go, and (in T.change) where they are in LDS
     const uint32_t place = n ? atomicAdd(&out.counts[(t * parts + part) << kCountShift], n) : 0u;
     __syncthreads();
     uint32_t before = upto - n, kept = 0;
 #pragma unroll
     for (int w = 0; w < kBinWG / 64; ++w) {
-      if (w < wave) before += s_wsum[w];
-      kept += s_wsum[w];
+      if (w < wave) before += T.wsum[w];
+      kept += T.wsum[w];
     }
-    if (t < P.nbuckets) s_change[t] = before;
+    if (t < G.nbuckets) s_before[t] = (uint16_t)before;
     __syncthreads();
-    Record *sorted = reinterpret_cast<Record *>(&s_shard[0][0]);
+    Record *sorted = reinterpret_cast<Record *>(&T.shard[0][0]);
 #pragma unroll
     for (int c = 0; c < RPT; ++c)
-      if (keep >> c & 1u) sorted[s_change[rec[c][3] >> P.bucket_shift] + rank[c]] = rec[c];
-    if (t < P.nbuckets) s_hist[t] = place - before;
+      if (keep >> c & 1u) sorted[s_before[rec[c][3] >> G.bucket_shift] + rank[c]] = rec[c];
+    if (t < G.nbuckets) s_hist[t] = place - before;
     __syncthreads();
 #pragma unroll 1
     for (uint32_t i = t; i < kept; i += kBinWG) {
       const Record x = sorted[i];
-      const uint32_t bucket = x[3] >> P.bucket_shift;
+      const uint32_t bucket = x[3] >> G.bucket_shift;
       append(x, bucket, s_hist[bucket] + i);
     }
     return;
@@ -444,11 +218,11 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
     for (int c = 0; c < RPT; ++c) {
       const uint32_t i = (uint32_t)(c * kBinWG + t);
-      const int q = s_u.list[i < here ? i : 0];
-      if (i < here) rank[c] = atomicAdd(&s_hist[s_shard[q & (L - 1)][q / L] >> P.bucket_shift], 1u);
+      const int q = T.list[i < here ? i : 0];
+      if (i < here) rank[c] = atomicAdd(&s_hist[(T.shard[q & (kRunL - 1)][q / kRunL] & P.shard_mask) >> G.bucket_shift], 1u);
     }
     __syncthreads();
-    if (t < P.nbuckets) {
+    if (t < G.nbuckets) {
       const uint32_t n = s_hist[t];
       if (n) s_hist[t] = atomicAdd(&out.counts[(t * parts + part) << kCountShift], n);
     }
@@ -457,16 +231,16 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     for (int c = 0; c < RPT; ++c) {
       const uint32_t i = (uint32_t)(c * kBinWG + t);
       if (i < here) {
-        const Record x = record(s_u.list[i]);
-        const uint32_t bucket = x[3] >> P.bucket_shift;
+        const Record x = record(T.list[i]);
+        const uint32_t bucket = x[3] >> G.bucket_shift;
         append(x, bucket, s_hist[bucket] + rank[c]);
       }
     }
     done += LCAP;
     if (done >= total) break;
     __syncthreads();
-    for (int b = t; b < P.nbuckets; b += kBinWG) s_hist[b] = 0;
-    list(done);
+    s_hist[t] = 0;
+    list_runs(T, head, first, done);
     __syncthreads();
   }
 }
@@ -667,12 +441,6 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
   }
 }
 
-int log2_of(uint64_t x) {
-  int n = 0;
-  while ((1ull << n) < x) ++n;
-  return n;
-}
-
 uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
 
 // Records of one region holding a share of n expected ones: the spread over
@@ -682,26 +450,13 @@ uint64_t region_cap(double expected, double slack) {
   return (uint64_t)std::ceil(expected * slack + 6.0 * std::sqrt(expected) + 64.0);
 }
 
-BitGeo bit_geo(const Geometry &g) {
-  BitGeo B;
-  B.z = (int)(g.k - g.s);
-  B.s_shift = 64 - 2 * (int)g.s;
-  B.H = (int)g.H;
-  B.slice = 64 / (int)g.H;
-  B.sw_log2 = log2_of(g.shard_words);
-  return B;
-}
-
 template <int W, int MK>
-hipError_t launch_bin(const SeqArgs &a, uint64_t nk, const BinGeo &P, const Bins &out, uint64_t *words,
-                      const BitGeo &B, hipStream_t st) {
-  // the list holds a tile's records in one pass at the expected 2 / (w + 1)
-  // per k-mer
-  constexpr int LCAP = W >= 16 && W <= 17 ? 1024 : 2048;
+hipError_t launch_bin(const SeqArgs &a, uint64_t nk, const RunGeo &P, const BinGeo &G, const Bins &out,
+                      uint64_t *words, const BitGeo &B, hipStream_t st) {
   const unsigned grid = (unsigned)((nk + kBinTile - 1) / kBinTile);
   const int aligned = ((uintptr_t)a.seq & 15u) == 0;
-  hipLaunchKernelGGL((bin_kernel<W, MK, LCAP>), dim3(grid), dim3(kBinWG), 0, st, a.seq, a.len, a.starts, aligned, P,
-                     out, words, B);
+  hipLaunchKernelGGL((bin_kernel<W, MK>), dim3(grid), dim3(kBinWG), 0, st, a.seq, a.len, a.starts, aligned, P, G, out,
+                     words, B);
   return hipGetLastError();
 }
 
@@ -728,34 +483,18 @@ hipError_t launch_apply(int slice_words_log2, const Bins &in, uint32_t s0, uint3
                                 : launch_apply_sb<SW, 13>(in, s0, nslices, regions, words, B, st);
 }
 
-// Compiled (w, m class) pairs: m = 16 at k = 31, and every w = k - m + 1 from
-// 6 on for m <= 16 (MK 1) and m > 16 (MK 2).  Below 6 a batch has a record
-// for every third k-mer or more.
-#define SBF_BIN_SETS(X)                                                                                  \
-  X(16, 0) X(6, 1) X(7, 1) X(8, 1) X(9, 1) X(10, 1) X(11, 1) X(12, 1) X(13, 1) X(14, 1) X(15, 1)          \
-  X(16, 1) X(17, 1) X(18, 1) X(19, 1) X(20, 1) X(21, 1) X(22, 1) X(23, 1) X(24, 1) X(25, 1) X(26, 1)      \
-  X(27, 1) X(28, 1) X(29, 1) X(30, 1) X(31, 1) X(32, 1) X(6, 2) X(7, 2) X(8, 2) X(9, 2) X(10, 2) X(11, 2) \
-  X(12, 2) X(13, 2) X(14, 2) X(15, 2) X(16, 2)
-
-bool bin_compiled(int w, int mk) {
-#define SBF_MATCH(W_, MK_) \
-  if (w == W_ && mk == MK_) return true;
-  SBF_BIN_SETS(SBF_MATCH)
-#undef SBF_MATCH
-  return false;
-}
-
-int mk_of(uint32_t k, uint32_t m) { return m > 16 ? 2 : k == 31 && m == 16 ? 0 : 1; }
-
 // k-mers of a record: 16, fewer where their bases would reach the low 4 bits
 int record_kmers(uint32_t k) { return std::min(16, 47 - (int)k); }
 
 }  // namespace
 
+bool runs_supported(const Geometry &g) {
+  return g.nshards <= (1ull << 32) && g.k <= 32 && g.H <= 8 && run_compiled((int)(g.k - g.m + 1), run_mk(g.k, g.m));
+}
+
 bool binned_plan(const Geometry &g, uint64_t len, bool lane_family, BinPlan &p) {
-  if (len < g.k || g.k > 32 || g.H > 8 || g.nshards > (1ull << 32)) return false;
+  if (len < g.k || !runs_supported(g)) return false;
   const int w = (int)(g.k - g.m + 1);
-  if (!bin_compiled(w, mk_of(g.k, g.m))) return false;
   const uint64_t nk = len - g.k + 1;
   const int words_bits = log2_of(g.nshards) + log2_of(g.shard_words);
   const uint64_t nbits = 64ull << words_bits;
@@ -807,15 +546,9 @@ hipError_t launch_insert_binned(const Geometry &g, uint64_t *words, const SeqArg
                                 hipStream_t st) {
   uint8_t *s = (uint8_t *)scratch;
   const BitGeo B = bit_geo(g);
-  const int mk = mk_of(g.k, g.m), w = (int)(g.k - g.m + 1);
-  BinGeo P;
-  P.k = (int)g.k;
-  P.m_shift = mk == 2 ? 64 - 2 * (int)g.m : 32 - 2 * (int)g.m;
-  P.nmax = record_kmers(g.k);
-  P.shard_mask = (uint32_t)(g.nshards - 1);
-  P.bucket_shift = p.slice_shift + p.bits2;
-  P.nbuckets = 1 << p.bits1;
-  P.part_mask = (int)p.parts - 1;
+  const int mk = run_mk(g.k, g.m), w = (int)(g.k - g.m + 1);
+  const RunGeo P = run_geo(g, record_kmers(g.k));
+  const BinGeo G{p.slice_shift + p.bits2, 1 << p.bits1, (int)p.parts - 1};
   const Bins b1{(Record *)(s + p.rec1), (uint32_t *)(s + p.counts1), (uint32_t)p.cap1};
   const Bins b2{(Record *)(s + p.rec2), (uint32_t *)(s + p.counts2), (uint32_t)p.cap2};
   const uint64_t nk_all = a.len - g.k + 1;
@@ -831,8 +564,8 @@ hipError_t launch_insert_binned(const Geometry &g, uint64_t *words, const SeqArg
     if (e != hipSuccess) return e;
     e = hipErrorInvalidValue;
 #define SBF_CALL(W_, MK_) \
-  if (w == W_ && mk == MK_) e = launch_bin<W_, MK_>(c, nk, P, b1, words, B, st);
-    SBF_BIN_SETS(SBF_CALL)
+  if (w == W_ && mk == MK_) e = launch_bin<W_, MK_>(c, nk, P, G, b1, words, B, st);
+    SBF_RUN_SETS(SBF_CALL)
 #undef SBF_CALL
     if (e != hipSuccess) return e;
     const uint32_t buckets = 1u << p.bits1;

@@ -329,6 +329,23 @@ int query_kernel_mode(const sbf_filter *f) {
                                              : sbf::kQueryLaneMode;
 }
 
+// True when a query of n_out k-mers takes the run kernels: the default
+// organisation and tile.  The lane kernels keep the batches between half a
+// round of the run kernels' resident workgroups (four per CU, 8192 k-mers
+// each) and a whole round of their own (12288 each): there a run kernel's
+// workgroups wait for their first bases together, or a few run a second tile.
+// Measured (us, runs against lane, 256 MiB filter): 3M k-mers 18.7/19.9, 5M
+// 25.9/24.2, 8M 34.5/32.1, 10M 55.0/41.0, 13M 63.1/66.7, 200M 490/547.
+bool by_runs(const sbf_filter *f, uint64_t n_out) {
+  if (f->query_mode != SBF_QUERY_LANE || f->query_lane_len != 0 || !sbf::runs_supported(f->g)) return false;
+  const Family fam = family(f);
+  if (fam == kLaneFamily) {
+    const uint64_t resident = 4ull * (uint64_t)f->num_cus;
+    return n_out <= resident * 4096 || n_out > resident * 12288;
+  }
+  return fam != kGenericFamily;
+}
+
 int run_query(sbf_filter *f, const SeqArgs &a, hipStream_t st, const sbf::LaunchShape *given = nullptr) {
   const int mode = query_kernel_mode(f);
   hipError_t e;
@@ -343,10 +360,18 @@ int run_query(sbf_filter *f, const SeqArgs &a, hipStream_t st, const sbf::Launch
     }
     ls.insert_lane_len = f->insert_lane_len;
     ls.query_lane_len = f->query_lane_len;
-    switch (family(f)) {
-      case kWideFamily: e = sbf::launch_query_wide(f->g, f->words, a, ls, st); break;
-      case kParamFamily: e = sbf::launch_query_param(f->g, f->words, a, ls, st); break;
-      default: e = sbf::launch_query_rolling(f->g, f->words, a, mode, ls, st); break;
+    if (by_runs(f, a.n_out)) {
+      switch (f->g.shard_words) {
+        case 4: e = sbf::launch_query_runs4(f->g, f->words, a, ls, st); break;
+        case 8: e = sbf::launch_query_runs8(f->g, f->words, a, ls, st); break;
+        default: e = sbf::launch_query_runs16(f->g, f->words, a, ls, st); break;
+      }
+    } else {
+      switch (family(f)) {
+        case kWideFamily: e = sbf::launch_query_wide(f->g, f->words, a, ls, st); break;
+        case kParamFamily: e = sbf::launch_query_param(f->g, f->words, a, ls, st); break;
+        default: e = sbf::launch_query_rolling(f->g, f->words, a, mode, ls, st); break;
+      }
     }
   } else {
     e = sbf::launch_query_generic(f->g, f->words, a, st);

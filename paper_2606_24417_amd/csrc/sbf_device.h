@@ -213,6 +213,15 @@ __device__ __forceinline__ uint64_t pair_swap64(uint64_t x) {
 // adding at the same time: the store pass loses them to a racing update and
 // the repair walk restores them, and the repair walk, whose plain loads race
 // only with its own atomic ORs, at worst repeats an OR.
-__device__ __forceinline__ void acquire_device() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+// One wave of the workgroup executes it (the caches are the CU's and the
+// XCD's, not the wave's) and the others wait: each invalidation makes the
+// waves that already run on the XCD fetch their lines, code included, again.
+// Measured on the query of an 8 Mbp contig: 53.6 us with every wave's
+// acquire, 34.5 with one per workgroup, 29.3 without any; of 200 Mbp 501, 490
+// and 484 us.
+__device__ __forceinline__ void acquire_device() {
+  if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  __syncthreads();
+}
 
 }  // namespace sbf

@@ -96,6 +96,15 @@ struct BinPlan {
 bool binned_plan(const Geometry &g, uint64_t len, bool lane_family, BinPlan &p);
 hipError_t launch_insert_binned(const Geometry &g, uint64_t *words, const SeqArgs &a, const BinPlan &p, void *scratch,
                                 hipStream_t st);
+// Run query kernels (query_runs.h), by shard size: H <= 8 and w = k-m+1 >= 6;
+// answers as bytes or bits.
+bool runs_supported(const Geometry &g);
+hipError_t launch_query_runs4(const Geometry &g, const uint64_t *words, const SeqArgs &a, const LaunchShape &ls,
+                              hipStream_t st);
+hipError_t launch_query_runs8(const Geometry &g, const uint64_t *words, const SeqArgs &a, const LaunchShape &ls,
+                              hipStream_t st);
+hipError_t launch_query_runs16(const Geometry &g, const uint64_t *words, const SeqArgs &a, const LaunchShape &ls,
+                               hipStream_t st);
 hipError_t launch_insert_generic(const Geometry &g, uint64_t *words, const SeqArgs &a, hipStream_t st);
 hipError_t launch_query_generic(const Geometry &g, const uint64_t *words, const SeqArgs &a, hipStream_t st);
 
