@@ -114,7 +114,9 @@ template <int W, int MK>
 __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) void bin_kernel(
     const uint8_t *__restrict__ seq, uint64_t len, const uint32_t *__restrict__ starts, int aligned16, RunGeo P,
     BinGeo G, Bins out, uint64_t *__restrict__ words, BitGeo B) {
-  constexpr int LCAP = run_list_cap<W, kBinWG>();
+  // a tile with more runs only appends in two goes, so the list is shorter
+  // than the query's
+  constexpr int LCAP = W >= 16 ? 1024 : W >= 11 ? 1536 : 2048;
   using Tile = RunTile<kBinWG, LCAP>;
   static_assert(LCAP % kBinWG == 0 && LCAP * 16 <= kRunL * kBinWG * 4, "whole records per lane, which fit over the shards");
   constexpr int RPT = LCAP / kBinWG;
@@ -337,7 +339,13 @@ __global__ __launch_bounds__(kSplitWG) __attribute__((amdgpu_waves_per_eu(4))) v
 // (slice - s0) * regions on; counts are indexed from slice 0.  The records are
 // taken in order of length (a counting sort of their indices), so that the
 // lanes of a wave finish together.
-template <int SW, int H, int SB>
+// With 8- and 16-word shards, whose bits are ORed one by one, sector c of shard
+// i is at place c ^ x(i) in LDS, x from i's low bits: the lanes of a wave, which
+// all OR the same sector at a time, then spread over all banks instead of a
+// quarter of them (16 words, 100 Mbp: 344 -> 305 us; no change with the four
+// 64-bit ORs per record of 4-word shards).
+// S > 0: s is known.
+template <int SW, int H, int SB, int S>
 __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4))) void apply_kernel(
     Bins in, uint32_t s0, uint32_t nslices, uint32_t regions, uint64_t *__restrict__ words, BitGeo B) {
   constexpr int SWL = SW == 4 ? 2 : SW == 8 ? 3 : 4;
@@ -346,44 +354,53 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
   constexpr int PIECES = WORDS / 2 / WG;  // 16-byte pieces per lane
   constexpr int SLICE = 64 / H;
   constexpr int PER = 8;                              // records sorted per lane
+  constexpr int CHUNK = PER * WG;
   __shared__ uint64_t s_words[WORDS];
-  __shared__ uint16_t s_list[PER * WG];
+  __shared__ uint16_t s_list[CHUNK];
   __shared__ uint32_t s_len[16];
   const int t = threadIdx.x;
   acquire_device();
-  uint4 *acc = reinterpret_cast<uint4 *>(s_words);
+  __syncthreads();
+  u32x4 *acc = reinterpret_cast<u32x4 *>(s_words);
+  auto swz = [](uint32_t shard) { return SW == 4 ? 0u : (shard >> (4 - SWL)) & 3u; };
+  auto region_count = [&](uint32_t slice, uint32_t g) {
+    const uint32_t n = in.counts[((uint64_t)(s0 + slice) * regions + g) << kCountShift];
+    return n < in.cap ? n : in.cap;
+  };
+  // 16 minus the k-mers of the lane's records i = t, t + WG, ..
+  auto lengths = [&](const Record *src, uint32_t here, uint32_t (&len)[PER]) {
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+      const uint32_t i = (uint32_t)(c * WG + t);
+      len[c] = 15u - (reinterpret_cast<const uint32_t *>(src + (i < here ? i : 0))[2] & 15u);
+    }
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int c = 0; c < PIECES; ++c) acc[c * WG + t] = u32x4{0, 0, 0, 0};
+  };
+  if (SW > 4) clear();
   for (uint32_t sl = blockIdx.x; sl < nslices; sl += gridDim.x) {
-    uint4 *line = reinterpret_cast<uint4 *>(words + ((uint64_t)(s0 + sl) << SB));
+    u32x4 *line = reinterpret_cast<u32x4 *>(words + ((uint64_t)(s0 + sl) << SB));
     // the slice's words are read now and used only at the end
-    uint4 old[PIECES];
+    u32x4 old[PIECES];
 #pragma unroll
     for (int c = 0; c < PIECES; ++c) old[c] = line[c * WG + t];
-#pragma unroll
-    for (int c = 0; c < PIECES; ++c) acc[c * WG + t] = make_uint4(0, 0, 0, 0);
+    if (SW == 4) clear();
     for (uint32_t g = 0; g < regions; ++g) {
-      uint32_t n = in.counts[((uint64_t)(s0 + sl) * regions + g) << kCountShift];
-      n = n < in.cap ? n : in.cap;
       const Record *src = in.rec + ((uint64_t)sl * regions + g) * in.cap;
-      for (uint32_t first = 0; first < n; first += PER * WG, src += PER * WG) {
-        const uint32_t here = n - first < PER * WG ? n - first : PER * WG;
+      const uint32_t n = region_count(sl, g);
+      for (uint32_t first = 0; first < n; first += CHUNK, src += CHUNK) {
+        const uint32_t here = n - first < CHUNK ? n - first : CHUNK;
         uint32_t len[PER], rank[PER];
-#pragma unroll
-        for (int c = 0; c < PER; ++c) {
-          const uint32_t i = (uint32_t)(c * WG + t);
-          len[c] = 15u - (reinterpret_cast<const uint32_t *>(src + (i < here ? i : 0))[2] & 15u);
-        }
+        lengths(src, here, len);
         if (t < 16) s_len[t] = 0;
         __syncthreads();  // also: the previous records are applied, the words are cleared
 #pragma unroll
         for (int c = 0; c < PER; ++c)
           if ((uint32_t)(c * WG + t) < here) rank[c] = atomicAdd(&s_len[len[c]], 1u);
         __syncthreads();
-        if (t < 16) {
-          uint32_t before = 0;
-          for (int j = 0; j < t; ++j) before += s_len[j];
-          __builtin_amdgcn_wave_barrier();
-          s_len[t] = before;
-        }
+        scan16(s_len);
         __syncthreads();
 #pragma unroll
         for (int c = 0; c < PER; ++c) {
@@ -392,17 +409,19 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
         }
         __syncthreads();
         uint32_t i = t;
-        Record r = src[s_list[i < here ? i : 0] & (PER * WG - 1)];
+        Record r = src[i < here ? s_list[i] : 0];
         while (i < here) {
           i += WG;
-          const Record next = src[s_list[i < here ? i : 0]];
-          uint64_t *shard = s_words + ((r[3] & ((WORDS >> SWL) - 1)) << SWL);
+          const Record next = src[i < here ? s_list[i] : 0];
+          const uint32_t shard = r[3] & ((WORDS >> SWL) - 1);
+          uint64_t *dst = s_words + (shard << SWL);
+          const uint32_t sx = swz(shard);
           const int count = (int)(r[2] & 15u) + 1 + B.z;
           uint32_t x = r[0], y = r[1], w = r[2];
           uint64_t m[4] = {0, 0, 0, 0};
 #pragma unroll 2
           for (int j = 0; j < count; ++j) {
-            const uint64_t g = smer_hash((((uint64_t)x << 32) | y) >> B.s_shift);
+            const uint64_t g = top_smer_hash<S>(x, y, B);
             x = __builtin_amdgcn_alignbit(x, y, 30);
             y = __builtin_amdgcn_alignbit(y, w, 30);
             w <<= 2;
@@ -412,16 +431,16 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
               if constexpr (SW == 4) {
                 m[h & 3] |= 1ull << (a & 63u);
               } else {
-                atomicOr(
-                    reinterpret_cast<uint32_t *>(shard + (h & 3) + 4 * ((a >> 6) & (SW / 4 - 1))) + ((a >> 5) & 1u),
-                    1u << (a & 31u));
+                // bytes from the shard on: sector, word group, half
+                const uint32_t off = ((((uint32_t)h & 3u) ^ sx) << 3) + (((a >> 1) & (32u * (SW / 4 - 1))) | ((a >> 3) & 4u));
+                atomicOr(reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(dst) + off), 1u << (a & 31u));
               }
             }
           }
           if constexpr (SW == 4) {
 #pragma unroll
             for (int h = 0; h < (H < 4 ? H : 4); ++h)
-              __hip_atomic_fetch_or(shard + h, m[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              __hip_atomic_fetch_or(dst + ((uint32_t)h ^ sx), m[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
           r = next;
         }
@@ -430,13 +449,13 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < PIECES; ++c) {
-      const uint4 a = acc[c * WG + t];
-      u32x4 v;
-      v[0] = old[c].x | a.x;
-      v[1] = old[c].y | a.y;
-      v[2] = old[c].z | a.z;
-      v[3] = old[c].w | a.w;
-      *(coherent_u32x4 *)(line + c * WG + t) = v;
+      const uint32_t piece = (uint32_t)(c * WG + t);  // words 2p and 2p+1 of a shard
+      const uint32_t sx = swz(piece >> (SWL - 1));
+      const u32x4 a = acc[piece ^ (sx >> 1)];
+      // another lane's place where sectors move: cleared by the lane that read it
+      if (SW > 4) acc[piece ^ (sx >> 1)] = u32x4{0, 0, 0, 0};
+      const u32x4 b = (sx & 1u) ? u32x4{a[2], a[3], a[0], a[1]} : a;
+      *(coherent_u32x4 *)(line + piece) = old[c] | b;
     }
   }
 }
@@ -462,14 +481,23 @@ hipError_t launch_bin(const SeqArgs &a, uint64_t nk, const RunGeo &P, const BinG
 
 template <int SW, int SB>
 hipError_t launch_apply_sb(const Bins &in, uint32_t s0, uint32_t nslices, uint32_t regions, uint64_t *words,
-                        const BitGeo &B, hipStream_t st) {
-#define SBF_APPLY(H_)                                                                                        \
-  case H_:                                                                                                   \
-    hipLaunchKernelGGL((apply_kernel<SW, H_, SB>), dim3(std::min(nslices, kApplyGrid << (13 - SB))),          \
-                       dim3(1 << (SB - 4)), 0, st, in, s0, nslices, regions, words, B);                      \
-    break;
+                           const BitGeo &B, hipStream_t st) {
+  const dim3 grid(std::min(nslices, kApplyGrid << (13 - SB))), wg(1 << (SB - 4));
+#define SBF_APPLY(H_, S_)                                                                                          \
+  hipLaunchKernelGGL((apply_kernel<SW, H_, SB, S_>), grid, wg, 0, st, in, s0, nslices, regions, words, B); break
   switch (B.H) {
-    SBF_APPLY(1) SBF_APPLY(2) SBF_APPLY(3) SBF_APPLY(4) SBF_APPLY(5) SBF_APPLY(6) SBF_APPLY(7) SBF_APPLY(8)
+    case 1: SBF_APPLY(1, 0);
+    case 2: SBF_APPLY(2, 0);
+    case 3: SBF_APPLY(3, 0);
+    case 4:
+      if (B.s_shift == 64 - 2 * 28) {
+        SBF_APPLY(4, 28);
+      }
+      SBF_APPLY(4, 0);
+    case 5: SBF_APPLY(5, 0);
+    case 6: SBF_APPLY(6, 0);
+    case 7: SBF_APPLY(7, 0);
+    case 8: SBF_APPLY(8, 0);
     default: return hipErrorInvalidValue;
   }
 #undef SBF_APPLY
@@ -489,7 +517,8 @@ int record_kmers(uint32_t k) { return std::min(16, 47 - (int)k); }
 }  // namespace
 
 bool runs_supported(const Geometry &g) {
-  return g.nshards <= (1ull << 32) && g.k <= 32 && g.H <= 8 && run_compiled((int)(g.k - g.m + 1), run_mk(g.k, g.m));
+  const int w = (int)(g.k - g.m + 1);
+  return g.nshards <= (1ull << 32) && g.k <= 32 && g.H <= 8 && run_compiled(w, run_mk(g.k, g.m));
 }
 
 bool binned_plan(const Geometry &g, uint64_t len, bool lane_family, BinPlan &p) {

@@ -16,13 +16,14 @@
 namespace sbf {
 namespace {
 
-// Hit bits of s-mers, shifted in from the right.
-template <int HMAX>
+// A run's shard in registers.  HC is H, or 0 where H (up to 8) is known only
+// at run time.
+template <int HC>
 struct Sectors {
   uint64_t w[4];
   // 1 where every bit of the s-mer with hash g is set in the shard
   __device__ __forceinline__ uint32_t test(uint64_t g, const BitGeo &B) const {
-    if constexpr (HMAX == 4) {
+    if constexpr (HC == 4) {
       const uint32_t lo = (uint32_t)g, hi = (uint32_t)(g >> 32);
       return (uint32_t)(w[0] >> (lo & 63u)) & (uint32_t)(w[1] >> ((lo >> 16) & 63u)) & (uint32_t)(w[2] >> (hi & 63u)) &
              (uint32_t)(w[3] >> ((hi >> 16) & 63u)) & 1u;
@@ -30,7 +31,7 @@ struct Sectors {
       uint32_t hit = 1u;
 #pragma unroll
       for (int h = 0; h < 8; ++h)
-        if (h < B.H) hit &= (uint32_t)(w[h & 3] >> ((uint32_t)(g >> (h * B.slice)) & 63u));
+        if (HC == 8 || h < B.H) hit &= (uint32_t)(w[h & 3] >> ((uint32_t)(g >> (h * (HC ? 64 / HC : B.slice))) & 63u));
       return hit;
     }
   }
@@ -38,7 +39,7 @@ struct Sectors {
 
 // A run's shard in the wave's LDS rows (pieces of 16 bytes, spread over the
 // banks by swz): the row's byte offset with the swizzle folded in.
-template <int SW, int HMAX>
+template <int SW, int HC>
 struct Row {
   const uint8_t *rows;
   uint32_t at;
@@ -46,9 +47,9 @@ struct Row {
     constexpr uint32_t GROUPS = 32u * (SW / 4 - 1);
     uint32_t hit = 1u;
 #pragma unroll
-    for (int h = 0; h < (HMAX == 4 ? 4 : 8); ++h) {
-      if (HMAX == 4 || h < B.H) {
-        const uint32_t a = (uint32_t)(g >> (HMAX == 4 ? 16 * h : h * B.slice));
+    for (int h = 0; h < (HC ? HC : 8); ++h) {
+      if (HC || h < B.H) {
+        const uint32_t a = (uint32_t)(g >> (h * (HC ? 64 / HC : B.slice)));
         const uint32_t off = (((a >> 1) & GROUPS) ^ (at ^ (uint32_t)(8 * (h & 2)))) | ((a >> 3) & 4u);
         hit &= *reinterpret_cast<const uint32_t *>(rows + off + 8 * (h & 1)) >> (a & 31u);
       }
@@ -73,21 +74,6 @@ struct Direct {
     return hit;
   }
 };
-
-// h_S of the s-mer at the top of (x, y); S > 0: s is known.
-template <int S>
-__device__ __forceinline__ uint64_t top_smer_hash(uint32_t x, uint32_t y, const BitGeo &B) {
-  if constexpr (S > 16 && S < 32) {
-    // below 2^62, v >> 30 has no high word
-    const uint32_t hi = x >> (64 - 2 * S);
-    uint32_t lo = __builtin_amdgcn_alignbit(x, y, 64 - 2 * S);
-    lo ^= __builtin_amdgcn_alignbit(hi, lo, 30);
-    const uint64_t v = (((uint64_t)hi << 32) | lo) * kSmerMul;
-    return v ^ (v >> 31);
-  } else {
-    return smer_hash((((uint64_t)x << 32) | y) >> B.s_shift);
-  }
-}
 
 // Answers of the wave's runs (one per lane) of n k-mers, whose bases are x, y,
 // w: bit r is k-mer r's.  The lanes take steps (uniform, at least n + z for
@@ -132,13 +118,13 @@ __device__ __forceinline__ uint32_t run_answers(const Shard &shard, uint32_t x, 
 
 constexpr int kRunWG = 256;
 
-template <int W, int MK, int SW, int HMAX, int S>
+template <int W, int MK, int SW, int HC, int S>
 __global__ __launch_bounds__(kRunWG) __attribute__((amdgpu_waves_per_eu(4))) void query_runs_kernel(
     const uint8_t *__restrict__ seq, uint64_t len, const uint32_t *__restrict__ starts, int aligned16,
     const uint64_t *__restrict__ words, RunGeo P, BitGeo B, uint8_t *__restrict__ out, uint64_t n_out, int out_aligned16,
     int out_packed, TileQueue tq) {
   constexpr int WG = kRunWG;
-  constexpr int LCAP = run_list_cap<W, kRunWG>();
+  constexpr int LCAP = run_list_cap<W>();
   constexpr int RPT = LCAP / WG;
   using Tile = RunTile<WG, LCAP>;
   __shared__ Tile T;
@@ -172,11 +158,7 @@ __global__ __launch_bounds__(kRunWG) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int c = 0; c < RPT; ++c)
           if ((uint32_t)(c * WG + t) < here) rank[c] = atomicAdd(&s_len[bin[c]], 1u);
         __syncthreads();
-        uint32_t before = 0;
-        if (t < 16)
-          for (int j = 0; j < t; ++j) before += s_len[j];
-        __syncthreads();
-        if (t < 16) s_len[t] = before;
+        scan16(s_len);
         __syncthreads();
 #pragma unroll
         for (int c = 0; c < RPT; ++c)
@@ -203,7 +185,7 @@ __global__ __launch_bounds__(kRunWG) __attribute__((amdgpu_waves_per_eu(4))) voi
           const uint32_t q2 = T.list[i + WG < here ? i + WG : 0];
           p = reinterpret_cast<const uint4 *>(words + 4ull * shard_of(q2));
           const uint4 lo2 = p[0], hi2 = p[1];
-          Sectors<HMAX> s;
+          Sectors<HC> s;
           s.w[0] = ((uint64_t)lo.y << 32) | lo.x;
           s.w[1] = ((uint64_t)lo.w << 32) | lo.z;
           s.w[2] = ((uint64_t)hi.y << 32) | hi.x;
@@ -268,7 +250,7 @@ __global__ __launch_bounds__(kRunWG) __attribute__((amdgpu_waves_per_eu(4))) voi
           fetch(sh[0]);  // the next round's lines (the last round's again after it)
           uint32_t x, y, w;
           run_bases(T, (int)at, x, y, w);
-          const Row<SW, HMAX> s{reinterpret_cast<const uint8_t *>(rows),
+          const Row<SW, HC> s{reinterpret_cast<const uint8_t *>(rows),
                                 (uint32_t)(lane * LPR * 16) | (swz(lane) << 4)};
           const uint32_t n = run_length1(T, (int)at) + 1u;
           const uint32_t ans = run_answers<S>(s, x, y, w, n, steps_of(n), B);
@@ -312,13 +294,13 @@ __global__ __launch_bounds__(kRunWG) __attribute__((amdgpu_waves_per_eu(4))) voi
   }
 }
 
-template <int W, int MK, int SW, int HMAX, int S>
+template <int W, int MK, int SW, int HC, int S>
 hipError_t query_runs(const Geometry &g, const uint64_t *words, const SeqArgs &a, const LaunchShape &ls,
                       hipStream_t st) {
   const uint64_t tile = (uint64_t)kRunWG * kRunL;
   const RunGeo P = run_geo(g, 16);
   const BitGeo B = bit_geo(g);
-  SBF_LAUNCH_TILES((query_runs_kernel<W, MK, SW, HMAX, S>), kRunWG, (a.n_out + tile - 1) / tile, 2, a.seq, a.len,
+  SBF_LAUNCH_TILES((query_runs_kernel<W, MK, SW, HC, S>), kRunWG, (a.n_out + tile - 1) / tile, 2, a.seq, a.len,
                    a.starts, (int)(((uintptr_t)a.seq & 15u) == 0), words, P, B, a.out, a.n_out,
                    (int)(((uintptr_t)a.out & 15u) == 0), a.packed);
   return hipSuccess;
@@ -332,10 +314,11 @@ hipError_t query_runs_any(const Geometry &g, const uint64_t *words, const SeqArg
   const int w = (int)(g.k - g.m + 1), mk = run_mk(g.k, g.m);
   // the paper's default s saves 3 of 22 instructions per s-mer
   if (w == 16 && mk == 0 && g.H == 4 && g.s == 28) return query_runs<16, 0, SW, 4, 28>(g, words, a, ls, st);
+  if (w == 16 && mk == 0 && g.H == 8) return query_runs<16, 0, SW, 8, 0>(g, words, a, ls, st);
 #define SBF_CALL(W_, MK_)                                                             \
   if (w == W_ && mk == MK_)                                                           \
     return g.H == 4 ? query_runs<W_, MK_, SW, 4, 0>(g, words, a, ls, st)              \
-                    : query_runs<W_, MK_, SW, 8, 0>(g, words, a, ls, st);
+                    : query_runs<W_, MK_, SW, 0, 0>(g, words, a, ls, st);
   SBF_RUN_SETS(SBF_CALL)
 #undef SBF_CALL
   return hipErrorInvalidValue;

@@ -336,6 +336,11 @@ int query_kernel_mode(const sbf_filter *f) {
 // workgroups wait for their first bases together, or a few run a second tile.
 // Measured (us, runs against lane, 256 MiB filter): 3M k-mers 18.7/19.9, 5M
 // 25.9/24.2, 8M 34.5/32.1, 10M 55.0/41.0, 13M 63.1/66.7, 200M 490/547.
+// The other families' tiles of 2048 or 4096 k-mers answer small batches sooner
+// (us, runs against them: (31,25,14,3) 100K 19.2/14.4, 300K 19.4/17.8;
+// (31,28,16,4) at 8 words 300K 20.6/18.6, at 16 words and H = 8 1M 39/35), and
+// with 8- or 16-word shards a tile of more runs than its list holds (w below
+// 8) tests them in memory.
 bool by_runs(const sbf_filter *f, uint64_t n_out) {
   if (f->query_mode != SBF_QUERY_LANE || f->query_lane_len != 0 || !sbf::runs_supported(f->g)) return false;
   const Family fam = family(f);
@@ -343,7 +348,9 @@ bool by_runs(const sbf_filter *f, uint64_t n_out) {
     const uint64_t resident = 4ull * (uint64_t)f->num_cus;
     return n_out <= resident * 4096 || n_out > resident * 12288;
   }
-  return fam != kGenericFamily;
+  if (fam == kGenericFamily) return false;
+  if (f->g.shard_words > 4 && f->g.k - f->g.m + 1 < 8) return false;
+  return n_out >= (f->g.shard_words > 4 && f->g.H > 4 ? 1ull << 21 : 1ull << 19);
 }
 
 int run_query(sbf_filter *f, const SeqArgs &a, hipStream_t st, const sbf::LaunchShape *given = nullptr) {

@@ -214,14 +214,18 @@ __device__ __forceinline__ uint64_t pair_swap64(uint64_t x) {
 // the repair walk restores them, and the repair walk, whose plain loads race
 // only with its own atomic ORs, at worst repeats an OR.
 // One wave of the workgroup executes it (the caches are the CU's and the
-// XCD's, not the wave's) and the others wait: each invalidation makes the
-// waves that already run on the XCD fetch their lines, code included, again.
+// XCD's, not the wave's) and waits for it; the workgroup's next barrier, which
+// every kernel has before its first filter access, holds the others.  Each
+// invalidation makes the waves that already run on the XCD fetch their lines,
+// code included, again.
 // Measured on the query of an 8 Mbp contig: 53.6 us with every wave's
 // acquire, 34.5 with one per workgroup, 29.3 without any; of 200 Mbp 501, 490
 // and 484 us.
 __device__ __forceinline__ void acquire_device() {
-  if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  __syncthreads();
+  if (threadIdx.x < 64) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  }
 }
 
 }  // namespace sbf

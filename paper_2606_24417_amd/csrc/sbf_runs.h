@@ -307,6 +307,35 @@ struct BitGeo {
   int sw_log2;  // log2 of the words per shard
 };
 
+// h_S of the s-mer at the top of (x, y); S > 0: s is known.
+template <int S>
+__device__ __forceinline__ uint64_t top_smer_hash(uint32_t x, uint32_t y, const BitGeo &B) {
+  if constexpr (S > 16 && S < 32) {
+    // below 2^62, v >> 30 has no high word
+    const uint32_t hi = x >> (64 - 2 * S);
+    uint32_t lo = __builtin_amdgcn_alignbit(x, y, 64 - 2 * S);
+    lo ^= __builtin_amdgcn_alignbit(hi, lo, 30);
+    const uint64_t v = (((uint64_t)hi << 32) | lo) * kSmerMul;
+    return v ^ (v >> 31);
+  } else {
+    return smer_hash((((uint64_t)x << 32) | y) >> B.s_shift);
+  }
+}
+
+// v[0 .. 15] in LDS: each becomes the sum of those before it (first wave).
+__device__ __forceinline__ void scan16(uint32_t *v) {
+  if (threadIdx.x < 64) {
+    const uint32_t own = v[threadIdx.x & 15u];
+    uint32_t incl = own;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+      const uint32_t o = __shfl_up(incl, d, 16);
+      if ((threadIdx.x & 15u) >= (uint32_t)d) incl += o;
+    }
+    if (threadIdx.x < 16) v[threadIdx.x] = incl - own;
+  }
+}
+
 // m classes (MK) of the compiled front ends: m = 16 (at k = 31), m <= 16, m > 16.
 inline int run_mk(uint32_t k, uint32_t m) { return m > 16 ? 2 : k == 31 && m == 16 ? 0 : 1; }
 
@@ -352,13 +381,10 @@ inline BitGeo bit_geo(const Geometry &g) {
   return B;
 }
 
-// Runs that a tile's list holds, a whole number per lane: the expected
-// 2 / (w + 1) per k-mer and some more.
-template <int W, int WG>
-constexpr int run_list_cap() {
-  constexpr int expected = W >= 16 ? 1024 : W >= 10 ? 1536 : 2048;  // per 8192 k-mers
-  return WG == 256 ? expected : expected * WG / 256 + WG;
-}
+// Runs that a tile's list holds, a whole number per lane: above the expected
+// 2 / (w + 1) per k-mer of 8192 (968 at w = 16) and its spread, for w from 8 on.
+template <int W>
+constexpr int run_list_cap() { return W >= 16 ? 1280 : W >= 11 ? 1536 : W == 10 ? 1792 : 2048; }
 
 }  // namespace
 }  // namespace sbf
