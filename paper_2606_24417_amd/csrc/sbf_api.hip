@@ -406,8 +406,7 @@ int record_starts(sbf_filter *f, const uint64_t *d_off, uint64_t nrec, uint64_t 
     if (rc) return rc;
   }
   uint32_t *w = (uint32_t *)s->ptr;
-  hipError_t e = sbf::launch_fill_u32(w, nw, 0u, st);
-  if (e == hipSuccess) e = sbf::launch_mark_record_starts(d_off, nrec, len, w, st);
+  hipError_t e = sbf::launch_mark_record_starts(d_off, nrec, len, w, st);
   if (e != hipSuccess) return hip_error(e, "record-start marking");
   *out = w;
   return SBF_OK;
@@ -926,11 +925,9 @@ int sbf_query_batch_dev_noalloc(sbf_filter *f, const char *d_seq, uint64_t len, 
   hipStream_t st = pick(f, stream);
   const uint32_t *starts = nullptr;
   if (nrec >= 2) {
-    // the bits of this batch only: clear its words (a fill kernel), then mark
+    // the words of this batch only
     uint32_t *w = scr + kNoAllocQueueWords;
-    const uint64_t nw = (len + 31) / 32;
-    hipError_t e = sbf::launch_fill_u32(w, nw, 0u, st);
-    if (e == hipSuccess) e = sbf::launch_mark_record_starts(d_off, nrec, len, w, st);
+    hipError_t e = sbf::launch_mark_record_starts(d_off, nrec, len, w, st);
     if (e != hipSuccess) return hip_error(e, "record-start marking");
     starts = w;
   }
@@ -946,8 +943,7 @@ int sbf_mark_record_starts_dev(const uint64_t *d_off, uint64_t nrec, uint64_t le
   if (len == 0) return ok();
   if (!d_off || !d_starts) return set_error(SBF_E_INVAL, "offsets or record-start bits are NULL");
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = sbf::launch_fill_u32(d_starts, (len + 31) / 32, 0u, st);
-  if (e == hipSuccess) e = sbf::launch_mark_record_starts(d_off, nrec, len, d_starts, st);
+  hipError_t e = sbf::launch_mark_record_starts(d_off, nrec, len, d_starts, st);
   if (e != hipSuccess) return hip_error(e, "record-start marking");
   return ok();
 }
@@ -1165,13 +1161,11 @@ void appendf(std::string &out, const char *fmt, ...) {
   out += buf;
 }
 
-// fill + mark record starts into s (allocated before any capture)
+// mark record starts into s (allocated before any capture)
 int mark_into(Scratch &s, const uint64_t *d_off, uint64_t nrec, uint64_t len, hipStream_t st, const uint32_t **out) {
   *out = nullptr;
   if (nrec < 2 || len == 0) return SBF_OK;
-  const uint64_t nw = (len + 31) / 32;
-  hipError_t e = sbf::launch_fill_u32((uint32_t *)s.ptr, nw, 0u, st);
-  if (e == hipSuccess) e = sbf::launch_mark_record_starts(d_off, nrec, len, (uint32_t *)s.ptr, st);
+  hipError_t e = sbf::launch_mark_record_starts(d_off, nrec, len, (uint32_t *)s.ptr, st);
   if (e != hipSuccess) return hip_error(e, "record-start marking");
   *out = (const uint32_t *)s.ptr;
   return SBF_OK;

@@ -128,8 +128,8 @@ hipError_t launch_count_nonzero_u8(const uint8_t *p, uint64_t n, uint64_t *count
 // sent to the shard finds all its bits set, and to *bits the set bits.
 hipError_t launch_estimate_fpr(const Geometry &g, const uint64_t *words, double *sum, uint64_t *bits,
                                hipStream_t st);
-// Set bit off[r] of `starts` for r = 1 .. nrec-1 (starts must be zeroed;
-// ceil(len/32) words).
+// Write the ceil(len/32) words of `starts`: bit off[r] set for r = 1 .. nrec-1
+// (offsets not decreasing), the others clear.
 hipError_t launch_mark_record_starts(const uint64_t *off, uint64_t nrec, uint64_t len, uint32_t *starts,
                                      hipStream_t st);
 
