@@ -38,7 +38,8 @@ PEAK_INT_TOPS = 39.3216      # 256 CU x 4 SIMD x 16 lanes x 2.4 GHz, 32-bit inte
 OPS_PER_KMER = {"insert": 46, "query": 63}
 KERNEL_SOURCES = ["paper_2606_24417_amd/csrc/kernels_rolling.hip", "paper_2606_24417_amd/csrc/kernels_wide.hip",
                   "paper_2606_24417_amd/csrc/sbf_tiles.h", "paper_2606_24417_amd/csrc/sbf_device.h",
-                  "paper_2606_24417_amd/csrc/sbf_segments.h"]
+                  "paper_2606_24417_amd/csrc/sbf_segments.h", "paper_2606_24417_amd/csrc/sbf_runs.h",
+                  "paper_2606_24417_amd/csrc/query_runs.h", "paper_2606_24417_amd/csrc/kernels_binned.hip"]
 
 
 def kernel_source_hash() -> str:
@@ -1018,14 +1019,19 @@ def measure(args, name, with_cpu):
     value = total_kmers / (ms_per_step * 1e-3)
     q_rate = n_q_kmers / (np.median(q_ms) * 1e-3)
     i_rate = n_ins_kmers / (np.median(ins_ms) * 1e-3)
-    # Roofline of the dominant work: the insert is two launches (store pass,
-    # then repair walk) unless it runs in atomic mode; the query is one.
+    # Roofline of the dominant work.  At the default tile these batches are
+    # binned (bin, split and apply kernels; the larger workload splits and
+    # applies its buckets in groups) and queried by runs; a given tile keeps
+    # the family's own kernels (store pass and repair walk, or one atomic pass).
     settings = f.get_launch()
     family = FAMILY_NAMES[f.variant]
     tile_i, tile_q = f.get_tile()
     settings.update({"family": family, "shard_words": S, "insert_kmers_per_lane": tile_i,
                      "query_kmers_per_lane": tile_q})
     ins_launches = 1 if settings["insert_mode"] == 1 else 2
+    given = [int(x) for x in args.tile.split(",")] if args.tile else [0, 0]
+    binned = ins_launches == 2 and given[0] == 0 and family != "generic" and not args.autotune
+    by_runs = settings["query_mode"] == 0 and given[1] == 0 and family != "generic" and not args.autotune
     if family == "wide-shard":
         q_kernel = "query_wide_kernel<31,28,16,4,%d,%d>" % (S, tile_q)
         ins_kernels = ("insert_wide_kernel<31,28,16,4,%d,%d> store pass + repair walk (two launches)" % (S, tile_i),
@@ -1039,6 +1045,10 @@ def measure(args, name, with_cpu):
             settings["query_mode"]] + "<31,28,16,4>"
         ins_kernels = ("insert_rolling_kernel<31,28,16,4> store pass + query_lane_kernel<31,28,16,4> repair walk",
                        "insert_rolling_kernel<31,28,16,4> (atomic)")
+    if by_runs:
+        q_kernel = "query_runs_kernel<16,0,%d,4,28>" % S
+    if binned:
+        ins_kernels = ("bin_kernel<16,0> + split_kernel + apply_kernel<%d,4>" % S, ins_kernels[1])
     in_cache = name != "out_of_cache"
 
     valu = None

@@ -26,8 +26,7 @@
 namespace sbf {
 namespace {
 
-constexpr int kBinWG = 256;
-constexpr int kBinTile = kBinWG * kRunL;    // k-mers per tile
+constexpr int kBinTile = 512 * kRunL;       // k-mers of the largest tile
 constexpr int kCountShift = 5;              // counters one 128-byte line apart
 constexpr int kXcds = 8;
 constexpr int kMaxBucketBits1 = 8;
@@ -110,24 +109,29 @@ __device__ __forceinline__ void apply_direct(Record r, uint64_t *words, BitGeo B
   }
 }
 
-template <int W, int MK>
-__global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) void bin_kernel(
+// Tiles of WG x 32 k-mers: 256 lanes, or 512 where there are 256 buckets.  A
+// tile appends 2 / (w + 1) records per k-mer; at 256 buckets a tile of 8192
+// k-mers appends less than four at a time to each, lines leave the L2 before
+// they are full and the pass writes 1.5 times its records (3 Gbp: 4.65 ms
+// with 256 lanes, 3.41 with 512; with 128 buckets 100 Mbp 0.113 and 0.120).
+template <int W, int MK, int WG>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void bin_kernel(
     const uint8_t *__restrict__ seq, uint64_t len, const uint32_t *__restrict__ starts, int aligned16, RunGeo P,
     BinGeo G, Bins out, uint64_t *__restrict__ words, BitGeo B) {
   // a tile with more runs only appends in two goes, so the list is shorter
   // than the query's
-  constexpr int LCAP = W >= 16 ? 1024 : W >= 11 ? 1536 : 2048;
-  using Tile = RunTile<kBinWG, LCAP>;
-  static_assert(LCAP % kBinWG == 0 && LCAP * 16 <= kRunL * kBinWG * 4, "whole records per lane, which fit over the shards");
-  constexpr int RPT = LCAP / kBinWG;
+  constexpr int LCAP = W >= 16 ? 4 * WG : W >= 11 || WG > 256 ? 6 * WG : 8 * WG;
+  using Tile = RunTile<WG, LCAP>;
+  static_assert(LCAP % WG == 0 && LCAP * 16 <= kRunL * WG * 4, "whole records per lane, which fit over the shards");
+  constexpr int RPT = LCAP / WG;
   __shared__ Tile T;
   __shared__ uint16_t s_before[1 << kMaxBucketBits1];  // a bucket's first record in the sorted tile
-  static_assert((1 << kMaxBucketBits1) <= kBinWG, "a bucket per lane");
+  static_assert((1 << kMaxBucketBits1) <= WG, "a bucket per lane");
 
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   uint32_t head, first, total;
-  find_runs<W, MK>(T, seq, len, (uint64_t)blockIdx.x * kBinTile, starts, aligned16 != 0, P, head, first, total);
+  find_runs<W, MK>(T, seq, len, (uint64_t)blockIdx.x * Tile::TILE, starts, aligned16 != 0, P, head, first, total);
   uint32_t *s_hist = T.change;  // records per bucket, then where they go
   s_hist[t] = 0;
   // each XCD appends to its own part of a bucket, so that the part's last
@@ -160,7 +164,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint32_t rank[RPT];
 #pragma unroll
     for (int c = 0; c < RPT; ++c) {
-      const uint32_t i = (uint32_t)(c * kBinWG + t);
+      const uint32_t i = (uint32_t)(c * WG + t);
       rec[c] = record(T.list[i < total ? i : 0]);
     }
     // A record equal to the one before it (long homopolymers and the like
@@ -168,7 +172,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint32_t keep = 0;
 #pragma unroll
     for (int c = 0; c < RPT; ++c) {
-      const bool here = (uint32_t)(c * kBinWG + t) < total;
+      const bool here = (uint32_t)(c * WG + t) < total;
       bool same = __shfl_up(rec[c][3], 1, 64) == rec[c][3] && lane > 0 && here;
       if (__ballot(same)) {
 #pragma unroll
@@ -193,7 +197,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     __syncthreads();
     uint32_t before = upto - n, kept = 0;
 #pragma unroll
-    for (int w = 0; w < kBinWG / 64; ++w) {
+    for (int w = 0; w < WG / 64; ++w) {
       if (w < wave) before += T.wsum[w];
       kept += T.wsum[w];
     }
@@ -206,7 +210,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     if (t < G.nbuckets) s_hist[t] = place - before;
     __syncthreads();
 #pragma unroll 1
-    for (uint32_t i = t; i < kept; i += kBinWG) {
+    for (uint32_t i = t; i < kept; i += WG) {
       const Record x = sorted[i];
       const uint32_t bucket = x[3] >> G.bucket_shift;
       append(x, bucket, s_hist[bucket] + i);
@@ -219,7 +223,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint32_t rank[RPT];
 #pragma unroll
     for (int c = 0; c < RPT; ++c) {
-      const uint32_t i = (uint32_t)(c * kBinWG + t);
+      const uint32_t i = (uint32_t)(c * WG + t);
       const int q = T.list[i < here ? i : 0];
       if (i < here) rank[c] = atomicAdd(&s_hist[(T.shard[q & (kRunL - 1)][q / kRunL] & P.shard_mask) >> G.bucket_shift], 1u);
     }
@@ -231,7 +235,7 @@ __global__ __launch_bounds__(kBinWG) __attribute__((amdgpu_waves_per_eu(4))) voi
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < RPT; ++c) {
-      const uint32_t i = (uint32_t)(c * kBinWG + t);
+      const uint32_t i = (uint32_t)(c * WG + t);
       if (i < here) {
         const Record x = record(T.list[i]);
         const uint32_t bucket = x[3] >> G.bucket_shift;
@@ -469,12 +473,13 @@ uint64_t region_cap(double expected, double slack) {
   return (uint64_t)std::ceil(expected * slack + 6.0 * std::sqrt(expected) + 64.0);
 }
 
-template <int W, int MK>
+template <int W, int MK, int WG>
 hipError_t launch_bin(const SeqArgs &a, uint64_t nk, const RunGeo &P, const BinGeo &G, const Bins &out,
                       uint64_t *words, const BitGeo &B, hipStream_t st) {
-  const unsigned grid = (unsigned)((nk + kBinTile - 1) / kBinTile);
+  constexpr uint64_t tile = (uint64_t)WG * kRunL;
+  const unsigned grid = (unsigned)((nk + tile - 1) / tile);
   const int aligned = ((uintptr_t)a.seq & 15u) == 0;
-  hipLaunchKernelGGL((bin_kernel<W, MK>), dim3(grid), dim3(kBinWG), 0, st, a.seq, a.len, a.starts, aligned, P, G, out,
+  hipLaunchKernelGGL((bin_kernel<W, MK, WG>), dim3(grid), dim3(WG), 0, st, a.seq, a.len, a.starts, aligned, P, G, out,
                      words, B);
   return hipGetLastError();
 }
@@ -580,6 +585,7 @@ hipError_t launch_insert_binned(const Geometry &g, uint64_t *words, const SeqArg
   const BinGeo G{p.slice_shift + p.bits2, 1 << p.bits1, (int)p.parts - 1};
   const Bins b1{(Record *)(s + p.rec1), (uint32_t *)(s + p.counts1), (uint32_t)p.cap1};
   const Bins b2{(Record *)(s + p.rec2), (uint32_t *)(s + p.counts2), (uint32_t)p.cap2};
+  const bool wide_tile = p.bits1 == kMaxBucketBits1 && p.bits2 > 0;
   const uint64_t nk_all = a.len - g.k + 1;
   for (uint64_t c0 = 0; c0 < nk_all; c0 += p.chunk) {
     // chunks start at whole tiles, so the sequence stays 16-byte aligned and
@@ -593,7 +599,9 @@ hipError_t launch_insert_binned(const Geometry &g, uint64_t *words, const SeqArg
     if (e != hipSuccess) return e;
     e = hipErrorInvalidValue;
 #define SBF_CALL(W_, MK_) \
-  if (w == W_ && mk == MK_) e = launch_bin<W_, MK_>(c, nk, P, G, b1, words, B, st);
+  if (w == W_ && mk == MK_)                                            \
+    e = wide_tile ? launch_bin<W_, MK_, 512>(c, nk, P, G, b1, words, B, st) \
+                  : launch_bin<W_, MK_, 256>(c, nk, P, G, b1, words, B, st);
     SBF_RUN_SETS(SBF_CALL)
 #undef SBF_CALL
     if (e != hipSuccess) return e;

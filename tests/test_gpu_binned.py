@@ -122,6 +122,27 @@ def test_several_chunks():
     assert np.array_equal(got[0], got[1])
 
 
+# filters from 2^34 bits on have 256 buckets and tiles of 16384 k-mers
+@pytest.mark.parametrize("k,s,m,H,n", [(21, 15, 11, 4, 70_000_017), (21, 15, 16, 2, 68_000_000)])
+def test_wide_tiles(k, s, m, H, n):
+    from paper_2606_24417_amd.sbf import INSERT_ATOMIC, Filter
+
+    print("case binned wide tile k=%d m=%d" % (k, m), flush=True)
+    seq = synth.background(n, 11).copy()
+    seq[1_000_000:1_400_000] = np.resize(seq[:40], 400_000)  # a crowded shard
+    seq[2_000_000:2_050_000] = ord("A")
+    seq[3_000_000::99_991] = ord("N")
+    d, got = dev(seq), []
+    for mode in (0, INSERT_ATOMIC):
+        f = Filter(k, s, m, H, 1 << 34)
+        f.set_insert_mode(mode)
+        f.insert(d)
+        torch.cuda.synchronize()
+        got.append(f.get_bits())
+        f.close()
+    assert np.array_equal(got[0], got[1])
+
+
 def test_captured_inserts():
     """sbf_graph_create captures the binned insert with its own scratch; a
     stream captured by the caller takes the two passes."""
