@@ -124,6 +124,15 @@ struct sbf_filter {
   std::unordered_map<hipStream_t, Scratch> queues;
   // records of binned inserts (inserts into one filter never overlap)
   Scratch bins;
+  // The end of the words' allocation: the counters of the first stream that
+  // needs some, then (small filters) the first records of binned inserts.  A
+  // device allocation of its own takes longer than a small insert or query.
+  uint8_t *tail = nullptr;
+  bool tail_queue_taken = false;
+
+  bool in_tail(const void *p) const {
+    return p && (p == tail || p == tail + 256);
+  }
 };
 
 namespace {
@@ -220,6 +229,11 @@ int launch_shape(sbf_filter *f, uint32_t wgs_per_cu, hipStream_t st, sbf::Launch
   {
     std::lock_guard<std::mutex> lk(f->mu);
     s = &f->queues[st];
+    if (!s->ptr && !f->tail_queue_taken) {
+      f->tail_queue_taken = true;
+      s->ptr = f->tail;
+      s->bytes = 256;
+    }
   }
   int rc = grow(*s, 256, "work-queue counters");
   if (rc) return rc;
@@ -242,7 +256,10 @@ void sbf::release_stream(sbf_filter *f, hipStream_t st) {
   for (auto *m : {&f->queues, &f->starts}) {
     auto it = m->find(st);
     if (it == m->end()) continue;
-    if (it->second.ptr) (void)hipFree(it->second.ptr);
+    if (f->in_tail(it->second.ptr))
+      f->tail_queue_taken = false;
+    else if (it->second.ptr)
+      (void)hipFree(it->second.ptr);
     m->erase(it);
   }
 }
@@ -258,18 +275,20 @@ bool binned(const sbf_filter *f, uint64_t len, sbf::BinPlan &plan) {
 }
 
 // Grow the record scratch s of binned inserts to plan.bytes.  False without
-// the memory (the insert then takes the two passes); the program keeps at
-// least as much free memory as the records take.
-bool grow_bins(Scratch &s, const sbf::BinPlan &plan) {
+// the memory (the insert then takes the two passes); of more than kFreeCheck
+// bytes the program keeps at least as much free memory as the records take.
+constexpr uint64_t kFreeCheck = 256ull << 20;
+bool grow_bins(const sbf_filter *f, Scratch &s, const sbf::BinPlan &plan) {
   if (s.bytes >= plan.bytes) return true;
   if (s.ptr) {
     // the old buffer may be in use by earlier inserts, on any stream
     if (hipDeviceSynchronize() != hipSuccess) return false;
-    (void)hipFree(s.ptr);
+    if (!f->in_tail(s.ptr)) (void)hipFree(s.ptr);
     s = Scratch();
   }
   size_t free_bytes = 0, total_bytes = 0;
-  if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || plan.bytes > free_bytes / 2 ||
+  if ((plan.bytes > kFreeCheck &&
+       (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || plan.bytes > free_bytes / 2)) ||
       grow(s, plan.bytes, "insert records") != SBF_OK) {
     (void)hipGetLastError();
     return false;
@@ -285,7 +304,7 @@ bool filter_bins(sbf_filter *f, const sbf::BinPlan &plan, hipStream_t st) {
     (void)hipGetLastError();
     return false;
   }
-  return grow_bins(f->bins, plan);
+  return grow_bins(f, f->bins, plan);
 }
 
 // `given` and `bins`: a graph's own launch counters and record scratch (bins
@@ -750,7 +769,19 @@ sbf_filter *sbf_create_ex(uint32_t k, uint32_t s, uint32_t m, uint32_t H, uint64
     return nullptr;
   }
   const uint64_t nwords = f->g.nshards * f->g.shard_words;
-  e = hipMalloc((void **)&f->words, nwords * sizeof(uint64_t));
+  // filters of 2 to 8 MiB: room for the records of about 16 bits per k-mer
+  const uint64_t filter_bytes = nwords * sizeof(uint64_t);
+  const uint64_t tail_bins =
+      filter_bytes >= (2ull << 20) && filter_bytes <= (8ull << 20) ? filter_bytes + filter_bytes / 4 : 0;
+  const uint64_t tail_at = (filter_bytes + 255) & ~255ull;
+  e = hipMalloc((void **)&f->words, tail_at + 256 + tail_bins);
+  if (e == hipSuccess) {
+    f->tail = (uint8_t *)f->words + tail_at;
+    if (tail_bins) {
+      f->bins.ptr = f->tail + 256;
+      f->bins.bytes = tail_bins;
+    }
+  }
   if (e != hipSuccess) {
     f->words = nullptr;
     hip_error(e, "filter allocation");
@@ -779,8 +810,8 @@ void sbf_destroy(sbf_filter *f) {
   for (auto &kv : f->starts)
     if (kv.second.ptr) (void)hipFree(kv.second.ptr);
   for (auto &kv : f->queues)
-    if (kv.second.ptr) (void)hipFree(kv.second.ptr);
-  if (f->bins.ptr) (void)hipFree(f->bins.ptr);
+    if (kv.second.ptr && !f->in_tail(kv.second.ptr)) (void)hipFree(kv.second.ptr);
+  if (f->bins.ptr && !f->in_tail(f->bins.ptr)) (void)hipFree(f->bins.ptr);
   for (PipeSlot &ps : f->pipe) {
     for (Scratch *d : {&ps.d_seq, &ps.d_out, &ps.d_off})
       if (d->ptr) (void)hipFree(d->ptr);
@@ -1195,7 +1226,7 @@ sbf_graph *sbf_graph_create(sbf_filter *f, int clear_first, const char *d_ins, u
   if (!rc && do_ins && ins_nrec > 1) rc = grow(g->starts_ins, (ins_len + 31) / 32 * 4, "record-start bits");
   if (!rc && do_q && q_nrec > 1) rc = grow(g->starts_q, (q_len + 31) / 32 * 4, "record-start bits");
   sbf::BinPlan plan;
-  if (!rc && do_ins && binned(f, ins_len, plan)) (void)grow_bins(g->bins, plan);
+  if (!rc && do_ins && binned(f, ins_len, plan)) (void)grow_bins(f, g->bins, plan);
   hipError_t e = hipSuccess;
   if (!rc) {
     e = hipStreamCreateWithFlags(&g->cap, hipStreamNonBlocking);
