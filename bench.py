@@ -1117,8 +1117,13 @@ def measure(args, name, with_cpu):
     i_mean = float(np.mean(ins_ms))
     roof_q = roofline("query", q_mean, n_q_kmers, 1)
     roof_q["kernel"] = q_kernel
+    ins_kernel = ins_kernels[0] if ins_launches == 2 else ins_kernels[1]
+    if binned:
+        # the counters' clearing and the bin pass, then a split and an apply
+        # launch per group of buckets: one in cache, 16 for the 8 GiB filter
+        ins_launches = 4 if in_cache else 34
     roof_i = roofline("insert", i_mean, n_ins_kmers, ins_launches)
-    roof_i["kernel"] = ins_kernels[0] if ins_launches == 2 else ins_kernels[1]
+    roof_i["kernel"] = ins_kernel
     if q_mean >= i_mean / ins_launches:
         roof, roof_other = roof_q, roof_i
     else:

@@ -248,7 +248,10 @@ int sbf_get_tile(const sbf_filter *f, uint32_t *insert_kmers_per_lane, uint32_t 
 int sbf_set_insert_mode(sbf_filter *f, int mode);
 
 /* How the rolling query kernel is organised:
- *   SBF_QUERY_LANE (default): each lane walks 48 consecutive k-mers, builds
+ *   SBF_QUERY_LANE (default): at the default tile length most batches are
+ *     tested one super-k-mer per lane (k-m >= 5, H <= 8: each lane loads its
+ *     super-k-mer's shard once and tests its s-mers); at a given tile length,
+ *     and for 4M to 12.6M k-mers, each lane walks 48 consecutive k-mers, builds
  *     the mask of each k-mer's (k-s+1)*H bits from its s-mers and tests it
  *     one k-mer later against the k-mer's shard, which the lane loads only
  *     where the shard changes (once per super-k-mer);
