@@ -11,13 +11,16 @@
 //      valid k-mers with one shard) and appends each as a 16-byte record (its
 //      bases, length and shard) to the bucket of its shard range;
 //   2. split_kernel (filters of more than 256 slices) splits each bucket into
-//      slices of 64 KB of the filter;
+//      slices of 32 or 64 KB of the filter;
 //   3. apply_kernel holds one slice in LDS, ORs the s-mer bits of the slice's
 //      records into it and writes the slice back once.
 // Every slice is read and written by one workgroup, so no update races with
 // another and no repair pass is needed.  A record that finds its bucket full
 // (a batch far from the expected spread over shards) is applied at once with
 // atomic ORs of the bits that are missing, before any slice is read.
+// Measured against the two passes (clear + insert): 100 Mbp into 256 MiB 880
+// -> 412 us, with 16-word shards 2159 -> 475, 3 Gbp into 8 GiB 29.8 -> 13.7 ms,
+// 1 Mbp into 2 MiB 76 -> 25 us.
 #include "sbf_runs.h"
 
 #include <algorithm>
@@ -255,7 +258,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void bi
 // of each.  The tiles of one bucket run on one XCD (workgroups go to the XCDs
 // in turn), so that the records appended to a slice gather in one L2, and a
 // tile's records are put in slice order in LDS first, so that consecutive
-// lanes append consecutive records.
+// lanes append consecutive records: the 12 M records of 100 Mbp take 76 us (5
+// TB/s read and written, the rate of a streaming copy) against 143 us appended
+// as they come.
 __global__ __launch_bounds__(kSplitWG) __attribute__((amdgpu_waves_per_eu(4))) void split_kernel(
     Bins in, Bins out, uint32_t b0, uint32_t tiles_per_region, int slice_shift, uint32_t slices_per_bucket,
     uint64_t *__restrict__ words, BitGeo B) {
@@ -342,7 +347,10 @@ __global__ __launch_bounds__(kSplitWG) __attribute__((amdgpu_waves_per_eu(4))) v
 // workgroup.  A slice's records lie in `regions` regions of in, from region
 // (slice - s0) * regions on; counts are indexed from slice 0.  The records are
 // taken in order of length (a counting sort of their indices), so that the
-// lanes of a wave finish together.
+// lanes of a wave finish together (320 -> 254 us for 100 Mbp, with fewer, larger
+// launches; 199 us now, 42 VALU instructions per k-mer at 55% of issue: a
+// workgroup waits between its sort, its records and its write-back, and four
+// per CU do not hide all of it).
 // With 8- and 16-word shards, whose bits are ORed one by one, sector c of shard
 // i is at place c ^ x(i) in LDS, x from i's low bits: the lanes of a wave, which
 // all OR the same sector at a time, then spread over all banks instead of a
