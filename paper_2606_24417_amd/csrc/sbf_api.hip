@@ -128,11 +128,10 @@ struct sbf_filter {
   // needs some, then (small filters) the first records of binned inserts.  A
   // device allocation of its own takes longer than a small insert or query.
   uint8_t *tail = nullptr;
+  uint64_t tail_bins = 0;  // bytes of records in it
   bool tail_queue_taken = false;
 
-  bool in_tail(const void *p) const {
-    return p && (p == tail || p == tail + 256);
-  }
+  bool in_tail(const void *p) const { return p && (p == tail || (tail_bins && p == tail + 256)); }
 };
 
 namespace {
@@ -777,6 +776,7 @@ sbf_filter *sbf_create_ex(uint32_t k, uint32_t s, uint32_t m, uint32_t H, uint64
   e = hipMalloc((void **)&f->words, tail_at + 256 + tail_bins);
   if (e == hipSuccess) {
     f->tail = (uint8_t *)f->words + tail_at;
+    f->tail_bins = tail_bins;
     if (tail_bins) {
       f->bins.ptr = f->tail + 256;
       f->bins.bytes = tail_bins;
