@@ -158,6 +158,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void bi
     else
       apply_direct(rec, words, B);
   };
+  // no run starts in the tile (records shorter than k, invalid bases): the
+  // list is empty and its storage still holds validity bits
+  if (total == 0) return;
   list_runs(T, head, first, 0);
   __syncthreads();
   if (total <= (uint32_t)LCAP) {

@@ -178,3 +178,30 @@ def test_captured_inserts():
         torch.cuda.synchronize()
         assert np.array_equal(f.get_bits(), want)
     f.close()
+
+
+# tiles in which no run starts: records shorter than k over several tiles, alone
+# and between valid ones, a last tile that holds only the end of the last
+# record, and valid bases that never make a k-mer
+@pytest.mark.parametrize("bits,S", [(1 << 24, 4), (1 << 27, 4), (1 << 27, 16)])
+@pytest.mark.parametrize("form", ["short", "between", "tail", "gaps"])
+def test_tiles_without_runs(form, bits, S):
+    print("case binned no runs", form, bits, S, flush=True)
+    rng = np.random.default_rng(31)
+    short = rng.integers(1, 31, size=14_000)
+    if form == "gaps":
+        seq = synth.uniform_acgt(200_000, 32).copy()
+        seq[20_000:180_000:30] = ord("N")
+        batch = (seq, None)
+    else:
+        if form == "short":
+            lens = short
+        elif form == "between":
+            lens = np.concatenate([[60_000], short[:7_000], [50_000], short[7_000:], [40_000]])
+        else:
+            lens = np.array([20 * 8192 - 40, 60, 29])
+        off = np.concatenate(([0], np.cumsum(lens))).astype(np.uint64)
+        batch = (synth.uniform_acgt(int(off[-1]), 33), off)
+    assert batch[0].size > 131072 + 31
+    check((31, 28, 16, 4, bits), S, [batch])
+    check((31, 28, 16, 4, bits), S, [(synth.uniform_acgt(150_000, 34), None), batch])
