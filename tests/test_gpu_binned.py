@@ -205,3 +205,42 @@ def test_tiles_without_runs(form, bits, S):
     assert batch[0].size > 131072 + 31
     check((31, 28, 16, 4, bits), S, [batch])
     check((31, 28, 16, 4, bits), S, [(synth.uniform_acgt(150_000, 34), None), batch])
+
+
+# crowded shards in tiles with more runs than their list holds (short windows),
+# with more shards than fit the table of a round, and with every shard size
+@pytest.mark.parametrize("k,s,m,H", [(31, 28, 16, 4), (21, 15, 16, 4), (31, 27, 16, 8), (32, 20, 1, 2)])
+@pytest.mark.parametrize("period", [3, 40, 1000, 5000])
+@pytest.mark.parametrize("bits,S", [(1 << 25, 4), (1 << 25, 16), (1 << 27, 8)])
+def test_crowded_parameters(bits, S, period, k, s, m, H):
+    print("case binned crowded", k, s, m, H, period, bits, S, flush=True)
+    seq = np.resize(synth.uniform_acgt(period, 60 + period), 700_000)
+    seq[300_000:300_005] = ord("N")
+    check((k, s, m, H, bits), S, [(seq, None), (synth.uniform_acgt(200_000, 61), None)])
+
+
+# A batch of few distinct super-k-mers takes about as long binned as with the
+# two passes that the set tile selects (1.2 times; 12 times where each record
+# that found its bucket full was tested in the filter by itself).
+@pytest.mark.parametrize("period", [40, 1000])
+def test_crowded_batches_are_not_slow(period):
+    from paper_2606_24417_amd import Filter
+
+    d = dev(np.resize(synth.uniform_acgt(period, 70 + period), 2_000_000))
+    f = Filter(31, 28, 16, 4, 1 << 25, shard_words=16)
+    took = []
+    for tile in (0, 16):
+        f.set_tile(tile, 0)
+        times = []
+        for _ in range(12):
+            f.clear()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            f.insert(d)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took.append(sorted(times)[len(times) // 2])
+    f.close()
+    print("binned %.3f ms, two passes %.3f ms" % tuple(took), flush=True)
+    assert took[0] < 2.5 * took[1]
