@@ -506,52 +506,47 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
     for (int c = 0; c < PIECES; ++c) acc[c * WG + t] = u32x4{0, 0, 0, 0};
   };
-  // OR the records i, i + WG, .. of the s_list order, the first in r.
-  auto take = [&](const Record *src, uint32_t here, uint32_t i, Record r, auto looks) {
+  // OR a record's s-mer bits into the slice.
+  auto take = [&](const Record &r, auto looks) {
     constexpr bool look = decltype(looks)::value;
-    while (i < here) {
-      i += WG;
-      const Record next = src[i < here ? s_list[i] : 0];
-      const uint32_t shard = r[3] & ((WORDS >> SWL) - 1);
-      uint64_t *dst = s_words + (shard << SWL);
-      const uint32_t sx = swz(shard);
-      const int count = (int)(r[2] & 15u) + 1 + B.z;
-      uint32_t x = r[0], y = r[1], w = r[2];
-      uint64_t m[4] = {0, 0, 0, 0};
+    const uint32_t shard = r[3] & ((WORDS >> SWL) - 1);
+    uint64_t *dst = s_words + (shard << SWL);
+    const uint32_t sx = swz(shard);
+    const int count = (int)(r[2] & 15u) + 1 + B.z;
+    uint32_t x = r[0], y = r[1], w = r[2];
+    uint64_t m[4] = {0, 0, 0, 0};
 // (unrolled by 2, the bit by bit ORs of 100 Mbp take 470 us instead of 457)
 #pragma unroll (SW > 4 ? 4 : 2)
-      for (int j = 0; j < count; ++j) {
-        const uint64_t g = top_smer_hash<S>(x, y, B);
-        x = __builtin_amdgcn_alignbit(x, y, 30);
-        y = __builtin_amdgcn_alignbit(y, w, 30);
-        w <<= 2;
-        uint32_t *p[H], bit[H], had[H];
+    for (int j = 0; j < count; ++j) {
+      const uint64_t g = top_smer_hash<S>(x, y, B);
+      x = __builtin_amdgcn_alignbit(x, y, 30);
+      y = __builtin_amdgcn_alignbit(y, w, 30);
+      w <<= 2;
+      uint32_t *p[H], bit[H], had[H];
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-          const uint32_t a = (uint32_t)(g >> (h * SLICE));
-          if constexpr (SW == 4) {
-            m[h & 3] |= 1ull << (a & 63u);
-          } else {
-            // bytes from the shard on: sector, word group, half
-            const uint32_t off = ((((uint32_t)h & 3u) ^ sx) << 3) + (((a >> 1) & (32u * (SW / 4 - 1))) | ((a >> 3) & 4u));
-            p[h] = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(dst) + off);
-            bit[h] = 1u << (a & 31u);
-            if constexpr (look) had[h] = __hip_atomic_load(p[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            else atomicOr(p[h], bit[h]);
-          }
-        }
-        if constexpr (SW > 4 && look) {
-#pragma unroll
-          for (int h = 0; h < H; ++h)
-            if (!(had[h] & bit[h])) atomicOr(p[h], bit[h]);
+      for (int h = 0; h < H; ++h) {
+        const uint32_t a = (uint32_t)(g >> (h * SLICE));
+        if constexpr (SW == 4) {
+          m[h & 3] |= 1ull << (a & 63u);
+        } else {
+          // bytes from the shard on: sector, word group, half
+          const uint32_t off = ((((uint32_t)h & 3u) ^ sx) << 3) + (((a >> 1) & (32u * (SW / 4 - 1))) | ((a >> 3) & 4u));
+          p[h] = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(dst) + off);
+          bit[h] = 1u << (a & 31u);
+          if constexpr (look) had[h] = __hip_atomic_load(p[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          else atomicOr(p[h], bit[h]);
         }
       }
-      if constexpr (SW == 4) {
+      if constexpr (SW > 4 && look) {
 #pragma unroll
-        for (int h = 0; h < (H < 4 ? H : 4); ++h)
-          __hip_atomic_fetch_or(dst + ((uint32_t)h ^ sx), m[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int h = 0; h < H; ++h)
+          if (!(had[h] & bit[h])) atomicOr(p[h], bit[h]);
       }
-      r = next;
+    }
+    if constexpr (SW == 4) {
+#pragma unroll
+      for (int h = 0; h < (H < 4 ? H : 4); ++h)
+        __hip_atomic_fetch_or(dst + ((uint32_t)h ^ sx), m[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   };
   if (SW > 4) clear();
@@ -569,14 +564,6 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
         const uint32_t here = n - first < CHUNK ? n - first : CHUNK;
         uint32_t len[PER], rank[PER];
         lengths(src, here, len);
-        // ORs of one LDS word go one by one.  The lanes of a wave are rarely of
-        // one shard, except in a batch with crowded shards: there a lane looks
-        // first whether the bit is set.
-        bool crowded = false;
-        if constexpr (SW > 4) {
-          const uint32_t shard = reinterpret_cast<const uint32_t *>(src + ((uint32_t)t < here ? t : 0))[3];
-          crowded = __popcll(__ballot(shard == (uint32_t)__builtin_amdgcn_readfirstlane((int)shard))) > 5;
-        }
         if (t < 16) s_len[t] = 0;
         __syncthreads();  // also: the previous records are applied, the words are cleared
 #pragma unroll
@@ -593,10 +580,18 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
         __syncthreads();
         uint32_t i = t;
         Record r = src[i < here ? s_list[i] : 0];
-        if (crowded)
-          take(src, here, i, r, std::true_type{});
-        else
-          take(src, here, i, r, std::false_type{});
+        while (i < here) {
+          i += WG;
+          const Record next = src[i < here ? s_list[i] : 0];
+          // ORs of one LDS word go one by one.  The lanes of a wave are rarely
+          // of one shard, except in a batch with crowded shards: there a lane
+          // looks first whether the bit is set.
+          if (SW > 4 && __popcll(__ballot(r[3] == (uint32_t)__builtin_amdgcn_readfirstlane((int)r[3]))) > 5)
+            take(r, std::true_type{});
+          else
+            take(r, std::false_type{});
+          r = next;
+        }
       }
     }
     __syncthreads();
