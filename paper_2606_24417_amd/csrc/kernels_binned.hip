@@ -660,6 +660,19 @@ hipError_t launch_apply(int slice_words_log2, const Bins &in, uint32_t s0, uint3
                                 : launch_apply_sb<SW, 13>(in, s0, nslices, regions, words, B, st);
 }
 
+// Expected records per k-mer of random sequence: runs of one minimizer in
+// windows of w, cut after nmax k-mers.  An m-mer is the minimum of at least l
+// successive windows with the probability (w-l) (1/(w+l-1) - 1/(w+l)) +
+// 1/(w+l-1), from its distances to the next smaller ones on both sides (2/(w+1)
+// for l = 1, the density of runs; 1/(2w-1) for l = w); each nmax k-mers of a
+// run make a record.
+double records_per_kmer(int w, int nmax) {
+  double sum = 0;
+  for (int l = 1; l <= w; l += nmax)
+    sum += (w - l) * (1.0 / (w + l - 1) - 1.0 / (w + l)) + 1.0 / (w + l - 1);
+  return sum;
+}
+
 // k-mers of a record: 16, fewer where their bases would reach the low 4 bits
 int record_kmers(uint32_t k) { return std::min(16, 47 - (int)k); }
 
@@ -694,8 +707,7 @@ bool binned_plan(const Geometry &g, uint64_t len, bool lane_family, BinPlan &p) 
   // a small batch does not fill eight parts of each bucket
   p.parts = p.bits2 == 0 && p.chunk <= kOnePartKmers ? 1 : kXcds;
   const int nmax = record_kmers(g.k);
-  double density = 2.0 / (w + 1) + 1.0 / kBinTile;
-  if (w > nmax) density *= 1.0 + (double)(w - nmax) / w;
+  const double density = records_per_kmer(w, nmax) + 1.0 / kBinTile;
   const double records = density * (double)p.chunk;
   const uint64_t buckets = 1ull << p.bits1, slices = 1ull << slice_bits;
   p.cap1 = region_cap(records / (double)(buckets * p.parts), 1.12);
