@@ -314,6 +314,14 @@ int run_insert(sbf_filter *f, const SeqArgs &a, hipStream_t st, const sbf::Launc
   hipError_t e;
   sbf::BinPlan plan;
   if (binned(f, a.len, plan) && (given ? bins && bins->bytes >= plan.bytes : filter_bins(f, plan, st))) {
+    if (!given) {
+      // the stream's counters are not used here, but a captured insert takes
+      // the two passes and may not allocate them: this insert may be its
+      // warm-up
+      sbf::LaunchShape ls;
+      int rc = launch_shape(f, f->insert_wgs_per_cu, st, ls);
+      if (rc) return rc;
+    }
     e = sbf::launch_insert_binned(f->g, f->words, a, plan, given ? bins->ptr : f->bins.ptr, st);
     if (e != hipSuccess) return hip_error(e, "insert kernel launch");
     return SBF_OK;

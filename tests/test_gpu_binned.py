@@ -244,3 +244,34 @@ def test_crowded_batches_are_not_slow(period):
     f.close()
     print("binned %.3f ms, two passes %.3f ms" % tuple(took), flush=True)
     assert took[0] < 2.5 * took[1]
+
+
+def test_capture_after_the_same_insert_as_warm_up():
+    """One insert on a stream prepares that stream for the capture of the same
+    insert, also where another stream has used the filter before."""
+    from paper_2606_24417_amd import Filter
+
+    seq, off = records(400_000, 500, 23)
+    p = oracle.Params(31, 28, 16, 4, 1 << 24)
+    want = oracle.insert(p, p.empty(), seq, off)
+    d, o = dev(seq), doff(off)
+    f = Filter(31, 28, 16, 4, 1 << 24)
+    f.query(d, o)
+    torch.cuda.synchronize()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        f.insert(d, o)
+    torch.cuda.synchronize()
+    cg = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(cg, stream=st):
+        f.clear()
+        f.insert(d, o)
+    for _ in range(3):
+        cg.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(f.get_bits(), want)
+        f.clear()
+        f.insert(d, o)
+        torch.cuda.synchronize()
+        assert np.array_equal(f.get_bits(), want)
+    f.close()
