@@ -237,9 +237,11 @@ int sbf_get_tile(const sbf_filter *f, uint32_t *insert_kmers_per_lane, uint32_t 
  *     instead: its super-k-mers are sorted by shard range into device scratch
  *     memory, about 1.2 times the filter's size plus 1 GiB at most (or 0.3 GB
  *     for small filters), kept until the filter is destroyed, and every part
- *     of the filter is then read and written once.  Without that much free
- *     memory, or while the stream is being captured (other than by
- *     sbf_graph_create), the two passes run;
+ *     of the filter is then read and written once.  A batch larger than those
+ *     before it takes a new scratch without waiting for them; the old ones,
+ *     together no larger than it, are freed by the next call that waits for the
+ *     device.  Without that much free memory, or while the stream is being
+ *     captured (other than by sbf_graph_create), the two passes run;
  *   SBF_INSERT_ATOMIC: one 64-bit atomic OR per shard word, as in the paper's
  *     Algorithm 1.
  * Both produce the same filter; the generic kernel always uses atomics. */

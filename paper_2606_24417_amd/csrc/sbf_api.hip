@@ -122,8 +122,12 @@ struct sbf_filter {
   std::unordered_map<hipStream_t, Scratch> starts;
   // work-queue counters of persistent launches, one set per stream
   std::unordered_map<hipStream_t, Scratch> queues;
-  // records of binned inserts (inserts into one filter never overlap)
+  // records of binned inserts (inserts into one filter never overlap), and the
+  // smaller buffers before it, which earlier inserts may still use: they are
+  // freed by the next call that waits for the device anyway
   Scratch bins;
+  void *outgrown[32];
+  int num_outgrown = 0;
   // The end of the words' allocation: the counters of the first stream that
   // needs some, then (small filters) the first records of binned inserts.  A
   // device allocation of its own takes longer than a small insert or query.
@@ -273,25 +277,52 @@ bool binned(const sbf_filter *f, uint64_t len, sbf::BinPlan &plan) {
          sbf::binned_plan(f->g, len, fam == kLaneFamily, plan);
 }
 
-// Grow the record scratch s of binned inserts to plan.bytes.  False without
-// the memory (the insert then takes the two passes); of more than kFreeCheck
-// bytes the program keeps at least as much free memory as the records take.
-constexpr uint64_t kFreeCheck = 256ull << 20;
-bool grow_bins(const sbf_filter *f, Scratch &s, const sbf::BinPlan &plan) {
-  if (s.bytes >= plan.bytes) return true;
-  if (s.ptr) {
-    // the old buffer may be in use by earlier inserts, on any stream
-    if (hipDeviceSynchronize() != hipSuccess) return false;
-    if (!f->in_tail(s.ptr)) (void)hipFree(s.ptr);
-    s = Scratch();
+// Allocations of a stream-ordered call: another thread's capture, or this
+// thread's of another stream, neither refuses them nor is spoilt by them.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool changed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  ~RelaxedCapture() {
+    if (changed) (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
+};
+
+// Allocate a record scratch of `bytes` for binned inserts.  False without the
+// memory (the insert then takes the two passes); of more than kFreeCheck bytes
+// the program keeps at least as much free memory as the records take.
+constexpr uint64_t kFreeCheck = 256ull << 20;
+bool new_bins(Scratch &s, uint64_t bytes) {
+  RelaxedCapture relaxed;
   size_t free_bytes = 0, total_bytes = 0;
-  if ((plan.bytes > kFreeCheck &&
-       (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || plan.bytes > free_bytes / 2)) ||
-      grow(s, plan.bytes, "insert records") != SBF_OK) {
+  if ((bytes > kFreeCheck &&
+       (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || bytes > free_bytes / 2)) ||
+      grow(s, bytes, "insert records") != SBF_OK) {
     (void)hipGetLastError();
     return false;
   }
+  return true;
+}
+
+// After the device has been waited for.
+void free_outgrown(sbf_filter *f) {
+  while (f->num_outgrown > 0) (void)hipFree(f->outgrown[--f->num_outgrown]);
+}
+
+// Grow the filter's record scratch to plan.bytes without waiting for earlier
+// inserts: the old buffer is put aside, and kept where the larger one is
+// refused.  A buffer is at least twice the one before, up to what the largest
+// batch takes, so that the outgrown ones together are no larger than it.
+bool grow_bins(sbf_filter *f, const sbf::BinPlan &plan) {
+  if (f->bins.bytes >= plan.bytes) return true;
+  if (f->num_outgrown == (int)(sizeof f->outgrown / sizeof f->outgrown[0])) return false;
+  uint64_t want = plan.bytes;
+  sbf::BinPlan most;
+  if (f->bins.ptr && sbf::binned_plan(f->g, 1ull << 48, family(f) == kLaneFamily, most))
+    want = std::max(want, std::min<uint64_t>(2 * f->bins.bytes, most.bytes));
+  Scratch s;
+  if (!new_bins(s, want) && (want == plan.bytes || !new_bins(s, plan.bytes))) return false;
+  if (f->bins.ptr && !f->in_tail(f->bins.ptr)) f->outgrown[f->num_outgrown++] = f->bins.ptr;
+  f->bins = s;
   return true;
 }
 
@@ -303,7 +334,7 @@ bool filter_bins(sbf_filter *f, const sbf::BinPlan &plan, hipStream_t st) {
     (void)hipGetLastError();
     return false;
   }
-  return grow_bins(f, f->bins, plan);
+  return grow_bins(f, plan);
 }
 
 // `given` and `bins`: a graph's own launch counters and record scratch (bins
@@ -636,6 +667,7 @@ int host_batch(sbf_filter *f, const char *seq, const uint64_t *off, uint64_t nre
                bool query) {
   // earlier stream-ordered work on any stream may still use the filter
   SBF_HIP(hipDeviceSynchronize(), "device synchronisation");
+  free_outgrown(f);
   int rc;
   if ((rc = ensure_pipe(f))) return rc;
   const uint64_t k = f->g.k;
@@ -820,6 +852,7 @@ void sbf_destroy(sbf_filter *f) {
   for (auto &kv : f->queues)
     if (kv.second.ptr && !f->in_tail(kv.second.ptr)) (void)hipFree(kv.second.ptr);
   if (f->bins.ptr && !f->in_tail(f->bins.ptr)) (void)hipFree(f->bins.ptr);
+  free_outgrown(f);
   for (PipeSlot &ps : f->pipe) {
     for (Scratch *d : {&ps.d_seq, &ps.d_out, &ps.d_off})
       if (d->ptr) (void)hipFree(d->ptr);
@@ -860,6 +893,7 @@ int sbf_set_bits(sbf_filter *f, const uint64_t *host_src, uint64_t nwords) {
   if (!host_src || nwords != sbf_num_words(f)) return set_error(SBF_E_INVAL, "need %llu words", (unsigned long long)sbf_num_words(f));
   if ((rc = set_device(f))) return rc;
   SBF_HIP(hipDeviceSynchronize(), "device synchronisation");
+  free_outgrown(f);
   SBF_HIP(hipMemcpy(f->words, host_src, nwords * 8, hipMemcpyHostToDevice), "copy filter to device");
   return ok();
 }
@@ -1234,7 +1268,7 @@ sbf_graph *sbf_graph_create(sbf_filter *f, int clear_first, const char *d_ins, u
   if (!rc && do_ins && ins_nrec > 1) rc = grow(g->starts_ins, (ins_len + 31) / 32 * 4, "record-start bits");
   if (!rc && do_q && q_nrec > 1) rc = grow(g->starts_q, (q_len + 31) / 32 * 4, "record-start bits");
   sbf::BinPlan plan;
-  if (!rc && do_ins && binned(f, ins_len, plan)) (void)grow_bins(f, g->bins, plan);
+  if (!rc && do_ins && binned(f, ins_len, plan)) (void)new_bins(g->bins, plan.bytes);
   hipError_t e = hipSuccess;
   if (!rc) {
     e = hipStreamCreateWithFlags(&g->cap, hipStreamNonBlocking);
@@ -1337,6 +1371,7 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
   const uint32_t keep_iw = f->insert_wgs_per_cu, keep_qw = f->query_wgs_per_cu;
   const uint32_t keep_il = f->insert_lane_len, keep_ql = f->query_lane_len;
   SBF_HIP(hipDeviceSynchronize(), "device synchronisation");
+  free_outgrown(f);
   bool backed_up = false;
   rc = grow(saved, sbf_num_words(f) * sizeof(uint64_t), "filter backup");
   if (!rc) {

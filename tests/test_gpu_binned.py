@@ -275,3 +275,79 @@ def test_capture_after_the_same_insert_as_warm_up():
         torch.cuda.synchronize()
         assert np.array_equal(f.get_bits(), want)
     f.close()
+
+
+def test_growing_batches_do_not_wait():
+    """A stream-ordered insert whose scratch grows returns while other work of
+    the device is still running, and the earlier insert's records stay."""
+    import time
+
+    from paper_2606_24417_amd import Filter
+
+    seqs = [synth.background(n, 90 + i) for i, n in enumerate((2_000_000, 5_000_000, 12_000_000))]
+    ds = [dev(x) for x in seqs]
+    p = oracle.Params(31, 28, 16, 4, 1 << 28)
+    want = p.empty()
+    for x in seqs:
+        want = oracle.insert(p, want, x)
+    warm = Filter(31, 28, 16, 4, 1 << 28)
+    warm.insert(ds[0])
+    f = Filter(31, 28, 16, 4, 1 << 28)
+    other = torch.cuda.Stream()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    torch.cuda._sleep(10_000_000)
+    b.record()
+    torch.cuda.synchronize()
+    cycles = int(10_000_000 * 500.0 / a.elapsed_time(b))  # half a second
+    busy = torch.cuda.Event()
+    with torch.cuda.stream(other):
+        torch.cuda._sleep(cycles)
+        busy.record()
+    t0 = time.perf_counter()
+    for d in ds:
+        f.insert(d)
+    took = time.perf_counter() - t0
+    still = not busy.query()
+    torch.cuda.synchronize()
+    print("three growing inserts returned after %.1f ms" % (took * 1e3), flush=True)
+    assert still and took < 0.25
+    assert np.array_equal(f.get_bits(), want)
+    f.insert(ds[0])
+    assert np.array_equal(f.get_bits(), want)
+    f.close()
+    warm.close()
+
+
+def test_growing_during_a_capture_elsewhere():
+    """A large insert on its own stream, while another stream is captured."""
+    from paper_2606_24417_amd import Filter
+
+    seq = synth.background(3_000_000, 95)
+    p = oracle.Params(31, 28, 16, 4, 1 << 28)
+    want = oracle.insert(p, p.empty(), seq)
+    d = dev(seq)
+    small = d[:100_000]
+    f, g = Filter(31, 28, 16, 4, 1 << 28), Filter(31, 28, 16, 4, 1 << 20)
+    st, own = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    f.insert(small, stream=own)  # the stream's counters
+    g.insert(small, stream=st)
+    torch.cuda.synchronize()
+    cg = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(cg, stream=st):
+        g.clear()
+        f.insert(d, stream=own)
+        g.insert(small)
+    torch.cuda.synchronize()
+    assert np.array_equal(f.get_bits(), want)
+    q = oracle.Params(31, 28, 16, 4, 1 << 20)
+    want_small = oracle.insert(q, q.empty(), seq[:100_000])
+    for _ in range(3):
+        cg.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(g.get_bits(), want_small)
+        g.insert(small)
+        torch.cuda.synchronize()
+    f.close()
+    g.close()
