@@ -235,9 +235,10 @@ int sbf_get_tile(const sbf_filter *f, uint32_t *insert_kmers_per_lane, uint32_t 
  *     (filters of at least 2^24 bits, H <= 8, k-m >= 5; from 131072 k-mers, and
  *     one k-mer for every 112 to 256 bits of filters above 16 MiB) is binned
  *     instead: its super-k-mers are sorted by shard range into device scratch
- *     memory, about 1.2 times the filter's size plus 1 GiB at most (or 0.3 GB
- *     for small filters), kept until the filter is destroyed, and every part
- *     of the filter is then read and written once.  A batch larger than those
+ *     memory, kept until the filter is destroyed, and every part of the filter
+ *     is then read and written once.  The scratch is at most 1 GiB plus 1.2
+ *     times the filter's size at k-m = 15, 1.7 times at k-m = 10, and 2.75
+ *     times at any k-m.  A batch larger than those
  *     before it takes a new scratch without waiting for them; the old ones,
  *     together no larger than it, are freed by the next call that waits for the
  *     device.  Without that much free memory, or while the stream is being

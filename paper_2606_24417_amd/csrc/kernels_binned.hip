@@ -48,8 +48,8 @@ constexpr int kSliceWordBits = SWB;          // a slice is 2^13 words: 64 KB
 constexpr int kSliceWords = 1 << kSliceWordBits;
 constexpr uint32_t kApplyGrid = 512 << (13-SWB);        // two workgroups per CU (64 KB of LDS each)
 
-// k-mers binned at a time: at least these (0.3 GB of records at w = 16), more
-// for a filter that has more memory itself
+// k-mers binned at a time: up to these, more for a filter that has more memory
+// itself
 constexpr uint64_t kMinChunkKmers = 1ull << 27;
 // batches up to these append to one part per bucket
 constexpr uint64_t kOnePartKmers = 1ull << 25;
@@ -702,33 +702,45 @@ bool binned_plan(const Geometry &g, uint64_t len, bool lane_family, BinPlan &p) 
   if (slice_bits < kMinSliceBits || slice_bits > kMaxBucketBits1 + kMaxBucketBits2) return false;
   p.bits1 = slice_bits <= kMaxBucketBits1 ? slice_bits : std::min(kMaxBucketBits1, (slice_bits + 1) / 2);
   p.bits2 = slice_bits - p.bits1;
-  p.chunk = std::min(nk, std::max(nbits / 15, kMinChunkKmers));
-  p.chunk = (p.chunk + kBinTile - 1) / kBinTile * kBinTile;
-  // a small batch does not fill eight parts of each bucket
-  p.parts = p.bits2 == 0 && p.chunk <= kOnePartKmers ? 1 : kXcds;
   const int nmax = record_kmers(g.k);
   const double density = records_per_kmer(w, nmax) + 1.0 / kBinTile;
-  const double records = density * (double)p.chunk;
   const uint64_t buckets = 1ull << p.bits1, slices = 1ull << slice_bits;
-  p.cap1 = region_cap(records / (double)(buckets * p.parts), 1.12);
-  p.cap2 = 0;
-  p.counts1 = 0;
-  uint64_t bytes = align256((buckets * p.parts * 4) << kCountShift);
-  p.counts2 = bytes;
-  p.group = (uint32_t)buckets;
-  if (p.bits2) {
-    bytes += align256((slices * 4) << kCountShift);
-    p.cap2 = region_cap(records / (double)slices, 1.4);
-    // buckets split and applied together: at most 1 GiB of records
-    const uint64_t per_bucket = (p.cap2 << p.bits2) * sizeof(Record);
-    while (p.group > (uint32_t)kXcds && p.group * per_bucket > (1ull << 30)) p.group /= 2;
-  }
-  p.count_words = bytes / 4;
-  p.rec1 = bytes;
-  bytes += align256(buckets * p.parts * p.cap1 * sizeof(Record));
-  p.rec2 = bytes;
-  if (p.bits2) bytes += align256(((uint64_t)p.group << p.bits2) * p.cap2 * sizeof(Record));
-  p.bytes = bytes;
+  auto lay_out = [&](uint64_t chunk) {
+    p.chunk = (chunk + kBinTile - 1) / kBinTile * kBinTile;
+    // a small batch does not fill eight parts of each bucket
+    p.parts = p.bits2 == 0 && p.chunk <= kOnePartKmers ? 1 : kXcds;
+    const double records = density * (double)p.chunk;
+    p.cap1 = region_cap(records / (double)(buckets * p.parts), 1.12);
+    p.cap2 = 0;
+    p.counts1 = 0;
+    uint64_t bytes = align256((buckets * p.parts * 4) << kCountShift);
+    p.counts2 = bytes;
+    p.group = (uint32_t)buckets;
+    if (p.bits2) {
+      bytes += align256((slices * 4) << kCountShift);
+      p.cap2 = region_cap(records / (double)slices, 1.4);
+      // buckets split and applied together: at most 1 GiB of records
+      const uint64_t per_bucket = (p.cap2 << p.bits2) * sizeof(Record);
+      while (p.group > (uint32_t)kXcds && p.group * per_bucket > (1ull << 30)) p.group /= 2;
+    }
+    p.count_words = bytes / 4;
+    p.rec1 = bytes;
+    bytes += align256(buckets * p.parts * p.cap1 * sizeof(Record));
+    p.rec2 = bytes;
+    if (p.bits2) bytes += align256(((uint64_t)p.group << p.bits2) * p.cap2 * sizeof(Record));
+    p.bytes = bytes;
+  };
+  // bits/15 k-mers take 9.6 times their records per k-mer, 2 / (w + 1), in
+  // filter sizes: 1.13 at w = 16, 1.6 at w = 11, 2.73 at w = 6.  Beyond 2.75
+  // times the filter plus 1 GiB (short windows into filters below 256 MiB) the
+  // batch takes equal parts that stay within it; each part reads and writes the
+  // whole filter, so a tighter bound would cost the larger filters time.
+  uint64_t chunk = std::min(nk, std::max(nbits / 15, kMinChunkKmers));
+  const uint64_t most = nbits / 8 * 11 / 4 + (1ull << 30);
+  for (lay_out(chunk); p.bytes > most; lay_out(chunk))
+    chunk = (uint64_t)(0.99 * (double)chunk * (double)most / (double)p.bytes);
+  const uint64_t nchunks = (nk + p.chunk - 1) / p.chunk;
+  if (nchunks > 1) lay_out((nk + nchunks - 1) / nchunks);
   return p.cap1 < (1ull << 31) && p.cap2 < (1ull << 31);
 }
 

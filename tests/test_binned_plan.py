@@ -53,3 +53,26 @@ def test_buckets_hold_the_records_of_random_sequence(bits, S, k, m):
     assert room > 1.1 * want, "room for %d records of %d" % (room, want)
     if p.bits2:
         assert p.cap2 << (p.bits1 + p.bits2) > 1.3 * want
+
+
+# The scratch that the header promises: at most 1 GiB plus 1.2 times the filter's
+# size at k-m = 15, 1.7 times at k-m = 10, 2.75 times at any, whatever the batch.
+@pytest.mark.parametrize("S", [4, 16])
+@pytest.mark.parametrize("log2_bits", range(24, 39))
+def test_scratch_stays_within_its_bound(log2_bits, S):
+    bits = 1 << log2_bits
+    planned = 0
+    for k, m in [(31, 16), (32, 17), (31, 18), (31, 12), (21, 11), (21, 12), (21, 14), (21, 16), (13, 4), (32, 1)]:
+        times = {16: 1.2, 11: 1.7}.get(k - m + 1 if k < 32 else 0, 2.75)
+        for length in (bits // 100, bits // 32, bits // 16, bits // 15, bits // 8, bits, 1 << 40):
+            p = plan(k, min(20, k), m, 4, bits, S, length)
+            if p is None:
+                continue
+            planned += 1
+            assert p.bytes <= times * bits / 8 + (1 << 30), (k, m, length)
+            assert p.rec2 <= p.bytes and p.chunk % 16384 == 0
+            # equal parts, smaller than the batch only by whole tiles
+            nk = length - k + 1
+            parts = -(-nk // p.chunk)
+            assert 0 <= p.chunk * parts - nk < 16384 * (parts + 1)
+    assert planned >= 20
