@@ -235,8 +235,8 @@ int sbf_get_tile(const sbf_filter *f, uint32_t *insert_kmers_per_lane, uint32_t 
  *     (filters of at least 2^24 bits, H <= 8, k-m >= 5; from 131072 k-mers, and
  *     one k-mer for every 112 to 256 bits of filters above 16 MiB) is binned
  *     instead: its super-k-mers are sorted by shard range into device scratch
- *     memory, kept until the filter is destroyed, and every part of the filter
- *     is then read and written once.  The scratch is at most 1 GiB plus 1.2
+ *     memory, kept until the filter is destroyed or sbf_release_scratch, and
+ *     every part of the filter is then read and written once.  The scratch is at most 1 GiB plus 1.2
  *     times the filter's size at k-m = 15, 1.7 times at k-m = 10, and 2.75
  *     times at any k-m.  A batch larger than those
  *     before it takes a new scratch without waiting for them; the old ones,
@@ -249,6 +249,10 @@ int sbf_get_tile(const sbf_filter *f, uint32_t *insert_kmers_per_lane, uint32_t 
 #define SBF_INSERT_TWO_PASS 0
 #define SBF_INSERT_ATOMIC 1
 int sbf_set_insert_mode(sbf_filter *f, int mode);
+/* Give back the scratch memory of binned inserts, for a filter that is only
+ * queried from now on (a later binned insert allocates it again).  Waits for
+ * all work on the device.  Graphs keep theirs until sbf_graph_destroy. */
+int sbf_release_scratch(sbf_filter *f);
 
 /* How the rolling query kernel is organised:
  *   SBF_QUERY_LANE (default): at the default tile length most batches are
@@ -285,7 +289,8 @@ int sbf_get_launch(const sbf_filter *f, uint32_t *insert_wgs_per_cu, uint32_t *q
  * the first and queries the second (device batches as in
  * sbf_insert_batch_dev / sbf_query_batch_dev; either may be NULL), with the
  * kernel organisation and launch shape in effect at creation.  The graph
- * owns its scratch (record-start bits, work-queue counters) and refers to
+ * owns its scratch (record-start bits, work-queue counters, the records of a
+ * binned insert: see SBF_INSERT_TWO_PASS) and refers to
  * the caller's buffers and to f, which must outlive it.  sbf_graph_launch
  * replays it on stream (NULL = HIP's null stream); replays on one stream are
  * ordered, replays on different streams must not overlap.  Returns NULL on

@@ -135,6 +135,14 @@ struct sbf_filter {
   uint64_t tail_bins = 0;  // bytes of records in it
   bool tail_queue_taken = false;
 
+  Scratch first_bins() const {
+    Scratch s;
+    if (tail_bins) {
+      s.ptr = tail + 256;
+      s.bytes = tail_bins;
+    }
+    return s;
+  }
   bool in_tail(const void *p) const { return p && (p == tail || (tail_bins && p == tail + 256)); }
 };
 
@@ -817,10 +825,7 @@ sbf_filter *sbf_create_ex(uint32_t k, uint32_t s, uint32_t m, uint32_t H, uint64
   if (e == hipSuccess) {
     f->tail = (uint8_t *)f->words + tail_at;
     f->tail_bins = tail_bins;
-    if (tail_bins) {
-      f->bins.ptr = f->tail + 256;
-      f->bins.bytes = tail_bins;
-    }
+    f->bins = f->first_bins();
   }
   if (e != hipSuccess) {
     f->words = nullptr;
@@ -904,6 +909,17 @@ int sbf_clear(sbf_filter *f, void *stream) {
   if ((rc = set_device(f))) return rc;
   hipError_t e = sbf::launch_fill_u64(f->words, sbf_num_words(f), 0ull, pick(f, stream));
   if (e != hipSuccess) return hip_error(e, "clear kernel launch");
+  return ok();
+}
+
+int sbf_release_scratch(sbf_filter *f) {
+  int rc;
+  if ((rc = check_filter(f))) return rc;
+  if ((rc = set_device(f))) return rc;
+  SBF_HIP(hipDeviceSynchronize(), "device synchronisation");
+  free_outgrown(f);
+  if (f->bins.ptr && !f->in_tail(f->bins.ptr)) (void)hipFree(f->bins.ptr);
+  f->bins = f->first_bins();
   return ok();
 }
 

@@ -65,6 +65,7 @@ SIGNATURES = {
     "sbf_set_variant": (_int, [_vp, _int]),
     "sbf_get_variant": (_int, [_vp]),
     "sbf_set_insert_mode": (_int, [_vp, _int]),
+    "sbf_release_scratch": (_int, [_vp]),
     "sbf_set_query_mode": (_int, [_vp, _int]),
     "sbf_set_staging_bytes": (_int, [_vp, _u64]),
     "sbf_set_launch": (_int, [_vp, _u32, _u32]),
@@ -205,6 +206,10 @@ class Filter:
 
     def set_insert_mode(self, mode: int):
         _check(lib().sbf_set_insert_mode(self._h, int(mode)))
+
+    def release_scratch(self):
+        """Give back the scratch memory of large inserts (waits for the device)."""
+        _check(lib().sbf_release_scratch(self._h))
 
     def set_query_mode(self, mode: int):
         _check(lib().sbf_set_query_mode(self._h, int(mode)))

@@ -351,3 +351,30 @@ def test_growing_during_a_capture_elsewhere():
         torch.cuda.synchronize()
     f.close()
     g.close()
+
+
+@pytest.mark.parametrize("bits", [1 << 24, 1 << 31])
+def test_scratch_is_given_back(bits):
+    """Growing inserts keep a record scratch (0.2 GB here), which
+    release_scratch returns; the filter goes on as before."""
+    from paper_2606_24417_amd import Filter
+
+    d = dev(synth.background(100_000_000 if bits > 1 << 24 else 4_000_000, 97))
+    f = Filter(31, 28, 16, 4, bits)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    for n in (2_000_000, d.numel() // 2, d.numel()):
+        f.insert(d[:n])
+    torch.cuda.synchronize()
+    kept = torch.cuda.mem_get_info()[0]
+    want = f.get_bits()
+    f.release_scratch()
+    after = torch.cuda.mem_get_info()[0]
+    print("free memory: %d, %d after inserts, %d after the release" % (before, kept, after), flush=True)
+    if bits > 1 << 24:
+        assert before - kept > 100 << 20
+    assert before - after < 8 << 20
+    f.clear()
+    f.insert(d)
+    assert np.array_equal(f.get_bits(), want)
+    f.close()
