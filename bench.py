@@ -1030,8 +1030,10 @@ def measure(args, name, with_cpu):
                      "query_kmers_per_lane": tile_q})
     ins_launches = 1 if settings["insert_mode"] == 1 else 2
     given = [int(x) for x in args.tile.split(",")] if args.tile else [0, 0]
-    binned = ins_launches == 2 and given[0] == 0 and family != "generic" and not args.autotune
-    by_runs = settings["query_mode"] == 0 and given[1] == 0 and family != "generic" and not args.autotune
+    binned = ins_launches == 2 and given[0] == 0 and family != "generic"
+    by_runs = settings["query_mode"] == 0 and given[1] == 0 and family != "generic"
+    if args.autotune:
+        binned, by_runs = "best insert: binned" in report, "best query: runs" in report
     if family == "wide-shard":
         q_kernel = "query_wide_kernel<31,28,16,4,%d,%d>" % (S, tile_q)
         ins_kernels = ("insert_wide_kernel<31,28,16,4,%d,%d> store pass + repair walk (two launches)" % (S, tile_i),

@@ -302,13 +302,19 @@ sbf_graph *sbf_graph_create(sbf_filter *f, int clear_first, const char *d_ins, u
 int sbf_graph_launch(sbf_graph *g, void *stream);
 void sbf_graph_destroy(sbf_graph *g);
 
-/* Autotuner: on the given device insert and query batches, time every insert
+/* Autotuner: on the given device insert and query batches, time the binned
+ * insert and the run query where the batches take them, and every insert
  * strategy, query organisation and compiled tile length (sbf_set_tile) with
  * one workgroup per tile and with persistent grids of 1, 2, 4 and 8
  * workgroups per CU (median of three runs after a warm-up) on f itself, whose
  * words are first saved to a temporary device buffer of the filter's size
  * and restored afterwards (f's contents are unchanged; the buffer must fit in
- * device memory), then apply the fastest settings to f.  A text report of
+ * device memory), then apply the fastest settings to f.  The family's own
+ * kernels take every later batch only where they beat the binned insert or the
+ * run query here; tuned on batches that take neither, f still picks by size, as
+ * at the default tile.  (Where SBF_INSERT_ATOMIC is fastest, as for batches of
+ * some 100000 k-mers, it holds for every later insert: tune on a batch like
+ * those to come.)  A text report of
  * every timing is written to report (NUL-terminated, truncated to
  * report_len; may be NULL).  Synchronous. */
 int sbf_autotune(sbf_filter *f, const char *d_ins, uint64_t ins_len, const uint64_t *d_ins_off, uint64_t ins_nrec,
@@ -325,7 +331,8 @@ int sbf_autotune(sbf_filter *f, const char *d_ins, uint64_t ins_len, const uint6
  * present, which counts them).  It returns the geometry with the lowest
  * insert + query time among those whose FPR is at most max_fpr, or, if none
  * is, the one with the lowest FPR, in *shard_words (required) with its tuned
- * tile lengths and its FPR (optional outputs, may be NULL).  The shard size
+ * tile lengths (for sbf_set_tile; 0 where the default, which picks the kernels
+ * by the batch, is to stay) and its FPR (optional outputs, may be NULL).  The shard size
  * changes the filter's bits, so the caller creates its filter with it
  * (sbf_create_ex).  A report of every trial is written to report as in
  * sbf_autotune.  Synchronous; each trial filter is freed before the next. */

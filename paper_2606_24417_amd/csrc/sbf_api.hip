@@ -113,6 +113,10 @@ struct sbf_filter {
   // k-mers per lane of the insert and query tiles (0: the family's default)
   uint32_t insert_lane_len = 0;
   uint32_t query_lane_len = 0;
+  // the family's own kernels take every batch (a given tile, or the autotuner
+  // found them faster than the binned insert or the run query)
+  bool insert_pinned = false;
+  bool query_pinned = false;
   int num_cus = 1;
   uint64_t staging = kDefaultStaging;
   // host entry points: chunk pipeline (created on first use)
@@ -278,10 +282,10 @@ void sbf::release_stream(sbf_filter *f, hipStream_t st) {
 namespace {
 
 // True when an insert of len bases takes the binned kernels: the two-pass
-// strategy at the family's default tile.
+// strategy, unless the family's kernels are pinned.
 bool binned(const sbf_filter *f, uint64_t len, sbf::BinPlan &plan) {
   const Family fam = family(f);
-  return f->insert_mode == SBF_INSERT_TWO_PASS && f->insert_lane_len == 0 && fam != kGenericFamily &&
+  return f->insert_mode == SBF_INSERT_TWO_PASS && !f->insert_pinned && fam != kGenericFamily &&
          sbf::binned_plan(f->g, len, fam == kLaneFamily, plan);
 }
 
@@ -395,7 +399,7 @@ int query_kernel_mode(const sbf_filter *f) {
 }
 
 // True when a query of n_out k-mers takes the run kernels: the default
-// organisation and tile.  The lane kernels keep the batches between half a
+// organisation, unless the family's kernels are pinned.  The lane kernels keep the batches between half a
 // round of the run kernels' resident workgroups (four per CU, 8192 k-mers
 // each) and a whole round of their own (12288 each): there a run kernel's
 // workgroups wait for their first bases together, or a few run a second tile.
@@ -407,7 +411,7 @@ int query_kernel_mode(const sbf_filter *f) {
 // with 8- or 16-word shards a tile of more runs than its list holds (w below
 // 8) tests them in memory.
 bool by_runs(const sbf_filter *f, uint64_t n_out) {
-  if (f->query_mode != SBF_QUERY_LANE || f->query_lane_len != 0 || !sbf::runs_supported(f->g)) return false;
+  if (f->query_mode != SBF_QUERY_LANE || f->query_pinned || !sbf::runs_supported(f->g)) return false;
   const Family fam = family(f);
   if (fam == kLaneFamily) {
     const uint64_t resident = 4ull * (uint64_t)f->num_cus;
@@ -1126,6 +1130,8 @@ int sbf_set_variant(sbf_filter *f, int variant) {
   // lane lengths belong to a family: back to the new family's defaults
   f->insert_lane_len = 0;
   f->query_lane_len = 0;
+  f->insert_pinned = false;
+  f->query_pinned = false;
   return ok();
 }
 
@@ -1148,6 +1154,8 @@ int sbf_set_tile(sbf_filter *f, uint32_t insert_kmers_per_lane, uint32_t query_k
                      insert_kmers_per_lane, query_kmers_per_lane);
   f->insert_lane_len = insert_kmers_per_lane;
   f->query_lane_len = query_kmers_per_lane;
+  f->insert_pinned = insert_kmers_per_lane != 0;
+  f->query_pinned = query_kmers_per_lane != 0;
   return ok();
 }
 
@@ -1366,9 +1374,10 @@ struct Batch {
 };
 
 // Autotuner of one filter: on the insert batch `ins` and query batch `q`,
-// time every insert strategy, query organisation, compiled lane length and
-// launch shape of the filter's kernel family (median of three runs after a
-// warm-up) on f itself, whose words are saved to a temporary device buffer
+// time the binned insert and the run query where the batches take them, and
+// every insert strategy, query organisation, compiled lane length and launch
+// shape of the filter's kernel family (median of three runs after a warm-up)
+// on f itself, whose words are saved to a temporary device buffer
 // and restored afterwards, then apply the fastest.  Generic kernels have
 // nothing to tune and are timed as they are.  Appends the report to rep and
 // returns the best insert and query times.
@@ -1386,6 +1395,7 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
   const int keep_imode = f->insert_mode, keep_qmode = f->query_mode;
   const uint32_t keep_iw = f->insert_wgs_per_cu, keep_qw = f->query_wgs_per_cu;
   const uint32_t keep_il = f->insert_lane_len, keep_ql = f->query_lane_len;
+  const bool keep_ip = f->insert_pinned, keep_qp = f->query_pinned;
   SBF_HIP(hipDeviceSynchronize(), "device synchronisation");
   free_outgrown(f);
   bool backed_up = false;
@@ -1427,7 +1437,9 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
     return SBF_OK;
   };
   float best_ins = 1e30f, best_q = 1e30f;
-  bool best_binned = false;
+  // the family's kernels stay pinned only if they beat the binned insert or
+  // the run query on these batches: others, of other sizes, keep the choice
+  bool tried_binned = false, best_binned = false, tried_runs = false, best_runs = false;
   int bi_mode = f->insert_mode, bq_mode = f->query_mode;
   uint32_t bi_shape = f->insert_wgs_per_cu, bq_shape = f->query_wgs_per_cu, bi_len = 0, bq_len = 0;
   const Family fam = family(f);
@@ -1454,8 +1466,10 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
     // the default of a large batch, where the compiled tile does not matter
     t->insert_mode = SBF_INSERT_TWO_PASS;
     t->insert_lane_len = 0;
+    t->insert_pinned = false;
     sbf::BinPlan plan;
     if (!rc && binned(t, ins.len, plan)) {
+      tried_binned = true;
       rc = time_it(true, best_ins);
       if (!rc) {
         line("insert binned: %.4f ms\n", best_ins);
@@ -1463,6 +1477,7 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
         best_binned = true;
       }
     }
+    t->insert_pinned = true;
     for (int mode : {SBF_INSERT_TWO_PASS, SBF_INSERT_ATOMIC}) {
       for (uint32_t len : ins_lens) {
         for (uint32_t sh : shapes) {
@@ -1487,6 +1502,25 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
       }
     }
     t->insert_lane_len = 0;
+    t->query_mode = SBF_QUERY_LANE;
+    t->query_pinned = false;
+    if (!rc && by_runs(t, q.len)) {
+      tried_runs = true;
+      for (uint32_t sh : shapes) {
+        t->query_wgs_per_cu = sh;
+        float ms;
+        rc = time_it(false, ms);
+        if (rc) break;
+        line("query  runs, workgroups/CU %u%s: %.4f ms\n", sh, sh ? "" : " (one per tile)", ms);
+        if (ms < best_q) {
+          best_q = ms;
+          bq_mode = SBF_QUERY_LANE;
+          bq_shape = sh;
+          best_runs = true;
+        }
+      }
+    }
+    t->query_pinned = true;
     for (int mode : {SBF_QUERY_LANE, SBF_QUERY_LEADER, SBF_QUERY_DIRECT}) {
       // the wide-shard kernels have one query organisation; lane lengths
       // apply to the lane-sequential query and to the wide kernels
@@ -1510,6 +1544,7 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
             bq_mode = mode;
             bq_shape = sh;
             bq_len = mode == SBF_QUERY_LANE ? len : 0;
+            best_runs = false;
           }
         }
       }
@@ -1521,7 +1556,10 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
         line("best insert: %s, %u k-mers/lane, workgroups/CU %u (%.4f ms)\n",
              bi_mode == SBF_INSERT_ATOMIC ? "atomic" : "two-pass", lane_len_effective(f, bi_len, true), bi_shape,
              best_ins);
-      line("best query: %s, %u k-mers/lane, workgroups/CU %u (%.4f ms)\n",
+      if (best_runs)
+        line("best query: runs, workgroups/CU %u (%.4f ms)\n", bq_shape, best_q);
+      else
+        line("best query: %s, %u k-mers/lane, workgroups/CU %u (%.4f ms)\n",
            wide ? wide_name : bq_mode == SBF_QUERY_LANE ? "lane" : bq_mode == SBF_QUERY_LEADER ? "leader" : "direct",
            bq_mode == SBF_QUERY_LANE ? lane_len_effective(f, bq_len, false) : 16u, bq_shape, best_q);
     }
@@ -1543,6 +1581,8 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
   f->query_wgs_per_cu = keep_qw;
   f->insert_lane_len = keep_il;
   f->query_lane_len = keep_ql;
+  f->insert_pinned = keep_ip;
+  f->query_pinned = keep_qp;
   if (rc) return rc;
   f->insert_mode = bi_mode;
   f->insert_wgs_per_cu = bi_shape;
@@ -1550,6 +1590,8 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
   f->query_mode = bq_mode;
   f->query_wgs_per_cu = bq_shape;
   f->query_lane_len = bq_len;
+  f->insert_pinned = tried_binned && !best_binned;
+  f->query_pinned = tried_runs && !best_runs;
   if (best_ins_out) *best_ins_out = best_ins;
   if (best_q_out) *best_q_out = best_q;
 #undef line
@@ -1660,8 +1702,9 @@ int sbf_autotune_geometry(uint32_t k, uint32_t s, uint32_t m, uint32_t H, uint64
     if (!rc) rc = fill_filter(f, ins);
     if (!rc) rc = count_present(f, neg, &present);
     uint32_t il = 0, ql = 0;
-    if (!rc) rc = sbf_get_tile(f, nullptr, &ql);
-    il = f->insert_lane_len;  // 0: the default, which may be the binned insert
+    // 0: the default, which picks the kernels by the batch
+    if (f->insert_pinned) il = f->insert_lane_len;
+    if (f->query_pinned) ql = f->query_lane_len;
     const int fam = sbf_get_variant(f);
     sbf_destroy(f);
     if (rc) break;

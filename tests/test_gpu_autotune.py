@@ -1,0 +1,84 @@
+"""A tuned filter keeps the binned insert and the run query: it answers and
+inserts about as fast as one that was never tuned, with the oracle's bits, also
+for batches much larger than those it was tuned on."""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def dev(x):
+    return torch.from_numpy(np.array(x, copy=True)).cuda()
+
+
+def one(x):
+    return dev(np.array([0, x.size], dtype=np.int64))
+
+
+def milliseconds(fn, n=15):
+    fn()
+    times = []
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        fn()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return sorted(times)[n // 2]
+
+
+# (16-word shards: the family's own kernels take 2.3 times as long for the
+# query, 4.5 times for the insert; at k = 21, m = 11 2.6 times for the query)
+@pytest.mark.parametrize("k,s,m,S", [(31, 28, 16, 4), (31, 28, 16, 16), (21, 15, 11, 4)])
+@pytest.mark.parametrize("tuned_on", [300_000, 2_000_000, 20_000_000])
+def test_tuned_filter_is_as_fast(tuned_on, k, s, m, S):
+    from paper_2606_24417_amd import Filter
+
+    ins, q = synth.background(20_000_000, 5), synth.background(20_000_000, 6)
+    d, dq = dev(ins), dev(q)
+    plain, tuned = Filter(k, s, m, 4, 1 << 28, shard_words=S), Filter(k, s, m, 4, 1 << 28, shard_words=S)
+    report = tuned.autotune(d[:tuned_on], one(ins[:tuned_on]), dq[:tuned_on], one(q[:tuned_on]))
+    print(report, flush=True)
+    if tuned_on > 2_000_000:
+        assert "query  runs" in report and "insert binned" in report
+    out = torch.empty(q.size, dtype=torch.uint8, device="cuda")
+    for name, run in (("insert", lambda f: f.insert(d)), ("query", lambda f: f.query(dq, out=out))):
+        if name == "insert" and tuned.get_launch()["insert_mode"] == 1:
+            continue  # the atomic strategy holds for every insert: they may overlap
+        a, b = milliseconds(lambda: run(plain)), milliseconds(lambda: run(tuned))
+        print("%s: untuned %.3f ms, tuned %.3f ms" % (name, a, b), flush=True)
+        assert b < 1.5 * a
+    p = oracle.Params(k, s, m, 4, 1 << 28, shard_words=S)
+    tuned.clear()
+    tuned.insert(d[:3_000_000])
+    assert np.array_equal(tuned.get_bits(), oracle.insert(p, p.empty(), ins[:3_000_000]))
+    plain.close()
+    tuned.close()
+
+
+def test_geometry_tuner_returns_lengths_that_apply():
+    from paper_2606_24417_amd import Filter, autotune_geometry
+
+    w = synth.in_cache_workload(scale=0.05)
+    ins, ioff = w["insert"]
+    q, qoff = w["query"]
+    a = [dev(ins), dev(ioff.view(np.int64)), dev(q), dev(qoff.view(np.int64))]
+    for k, s, m, H in ((31, 28, 16, 4), (31, 27, 16, 4), (21, 15, 11, 4)):
+        res = autotune_geometry(k, s, m, H, w["bits"], *a, a[2], a[3], max_fpr=1.0)
+        assert "query  runs" in res["report"]
+        f = Filter(k, s, m, H, w["bits"], shard_words=res["shard_words"])
+        f.set_tile(res["insert_kmers_per_lane"], res["query_kmers_per_lane"])
+        f.close()
