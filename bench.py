@@ -649,14 +649,14 @@ def bench_sweep(args):
     in-cache workload (scaled by --scale): per point, the FPR on the negative
     reads, a zero-false-negative check on genome k-mers, and insert and query
     kernel time of the run-time parameter kernels (one kernel family over the
-    whole grid, so that times compare parameters) and of the family the
-    library picks by itself (compiled lane or wide-shard kernels where they
-    exist).  Then the shard geometries (4, 8, 16 words) at (28, 16, 4) with
-    every family that runs them.  The FPR against filter size is the
+    whole grid, so that times compare parameters) and of the kernels the
+    library picks by itself, with a check that both give the same answers.
+    Then the shard geometries (4, 8, 16 words) at (28, 16, 4) with the
+    library's choice and every family that runs them.  The FPR against filter size is the
     fpr_curve workload."""
     import torch
 
-    from paper_2606_24417_amd import VARIANT_AUTO, VARIANT_PARAM, Filter
+    from paper_2606_24417_amd import VARIANT_AUTO, VARIANT_PARAM, VARIANT_ROLLING, Filter
 
     t0 = time.perf_counter()
     w = synth.in_cache_workload(args.scale)
@@ -715,28 +715,30 @@ def bench_sweep(args):
         f.set_insert_mode(0)
         row = {"s": s_, "m": m_, "H": h_, "fpr": fp / max(1, neg_kmers), "param_insert_ms": pi,
                "param_insert_atomic_ms": pa, "param_query_ms": pq, "zero_fn": no_fn}
+        # the kernels the library picks for this point (binned insert and run
+        # query from k-m = 5 on, else a compiled family's): their times, and
+        # the same answers as the run-time parameter kernels
         f.variant = VARIANT_AUTO
-        if f.variant != VARIANT_PARAM:
-            # a compiled family for this point: its own times, and the same
-            # answers as the run-time parameter kernels
-            ai, aq = timed(f, d_ref)
-            row.update({"variant": FAMILY_NAMES[f.variant], "insert_ms": ai, "query_ms": aq,
-                        "answers_equal": bool(torch.equal(d_out, d_ref))})
-        else:
-            row.update({"variant": FAMILY_NAMES[VARIANT_PARAM], "insert_ms": pi, "query_ms": pq})
+        ai, aq = timed(f, d_ref)
+        row.update({"variant": FAMILY_NAMES[f.variant], "insert_ms": ai, "query_ms": aq,
+                    "answers_equal": bool(torch.equal(d_out, d_ref))})
         rows.append(row)
         f.close()
         if (i + 1) % 48 == 0:
             print("[bench] sweep %d/%d points" % (i + 1, len(grid)), file=sys.stderr, flush=True)
-    # shard geometry (4, 8, 16 words per shard) at (28, 16, 4), each with
-    # every family that runs it
+    # shard geometry (4, 8, 16 words per shard) at (28, 16, 4), each with the
+    # library's choice (binned insert, run query) and with every family that
+    # runs it (the lane kernels by their tile)
     geometry = []
-    for S, variants in ((4, (1, 4, 2)), (8, (3, 4, 2)), (16, (3, 4, 2))):
+    for S, variants in ((4, (0, 1, 4, 2)), (8, (0, 3, 4, 2)), (16, (0, 3, 4, 2))):
         for variant in variants:
             f = Filter(k, 28, 16, 4, w["bits"], shard_words=S)
             f.variant = variant
+            if variant == VARIANT_ROLLING:
+                f.set_tile(64, 48)
             ti, tq = timed(f, d_out)
-            geometry.append({"shard_words": S, "kernels": FAMILY_NAMES[variant], "filter_bits": f.num_bits,
+            geometry.append({"shard_words": S, "kernels": FAMILY_NAMES[variant] if variant else "default",
+                             "filter_bits": f.num_bits,
                              "fpr": int(d_out[neg0:].sum().item()) / max(1, neg_kmers), "insert_ms": ti,
                              "query_ms": tq})
             f.close()
@@ -746,7 +748,7 @@ def bench_sweep(args):
     fastest = min(rows, key=lambda r: r["param_insert_ms"] + r["param_query_ms"])
     res = {"metric": "sweep: FPR and insert/query kernel ms per (s,m,H) at k=31, 16 bits per k-mer",
            "unit": "fpr", "points": len(rows), "zero_false_negatives_everywhere": all_ok,
-           "compiled_and_param_answers_equal": same, "best_fpr": best, "fastest_param": fastest,
+           "default_and_param_answers_equal": same, "best_fpr": best, "fastest_param": fastest,
            "at_28_16_4": next((r for r in rows if (r["s"], r["m"], r["H"]) == (28, 16, 4)), None),
            "rows": rows, "geometry": geometry,
            "config": {"workload": w["name"] + " (scale %g)" % args.scale, "filter_bits": w["bits"],
@@ -1021,8 +1023,9 @@ def measure(args, name, with_cpu):
     i_rate = n_ins_kmers / (np.median(ins_ms) * 1e-3)
     # Roofline of the dominant work.  At the default tile these batches are
     # binned (bin, split and apply kernels; the larger workload splits and
-    # applies its buckets in groups) and queried by runs; a given tile keeps
-    # the family's own kernels (store pass and repair walk, or one atomic pass).
+    # applies its buckets in groups) and queried by runs; a given tile, or the
+    # wide-shard or run-time parameter family, keeps the family's own kernels
+    # (store pass and repair walk, or one atomic pass).
     settings = f.get_launch()
     family = FAMILY_NAMES[f.variant]
     tile_i, tile_q = f.get_tile()
@@ -1032,7 +1035,9 @@ def measure(args, name, with_cpu):
     given = [int(x) for x in args.tile.split(",")] if args.tile else [0, 0]
     binned = ins_launches == 2 and given[0] == 0 and family != "generic"
     by_runs = settings["query_mode"] == 0 and given[1] == 0 and family != "generic"
-    if args.autotune:
+    if args.variant in (3, 4):
+        binned = by_runs = False
+    elif args.autotune:
         binned, by_runs = "best insert: binned" in report, "best query: runs" in report
     if family == "wide-shard":
         q_kernel = "query_wide_kernel<31,28,16,4,%d,%d>" % (S, tile_q)

@@ -51,8 +51,8 @@ extern "C" {
 
 /* Kernel families (sbf_set_variant). */
 #define SBF_VARIANT_AUTO 0    /* the fastest super-k-mer kernels for (k,s,m,H) and the shard size, else generic */
-#define SBF_VARIANT_ROLLING 1 /* super-k-mer kernels: lane kernels for 4-word shards, wide-shard kernels for 8/16,
-                                 run-time parameter kernels for other (k,s,m,H) */
+#define SBF_VARIANT_ROLLING 1 /* as AUTO, but refused where only the generic kernels exist: lane kernels for 4-word
+                                 shards, wide-shard kernels for 8/16, run-time parameter kernels for other (k,s,m,H) */
 #define SBF_VARIANT_GENERIC 2 /* one k-mer per lane, run-time k, s, m, H */
 #define SBF_VARIANT_WIDE 3    /* wide-shard (two-phase, whole-line) super-k-mer kernels, also for 4-word shards */
 #define SBF_VARIANT_PARAM 4   /* two-phase super-k-mer kernels with run-time k <= 32, s, m, H <= 8 (any shard size) */
@@ -199,8 +199,11 @@ int sbf_query_marked_dev(sbf_filter *f, const char *d_seq, uint64_t len, const u
  * SBF_VARIANT_WIDE and SBF_VARIANT_PARAM fail with SBF_E_INVAL when no such
  * kernel exists for the filter's (k,s,m,H) and shard size (the wide-shard
  * kernels are compiled for a few parameter sets; the run-time parameter
- * kernels take k <= 32 and H <= 8).  Every family gives bit-identical
- * filters and answers.  Changing the family resets the tile lengths
+ * kernels take k <= 32 and H <= 8).  SBF_VARIANT_AUTO and SBF_VARIANT_ROLLING
+ * also take the binned insert and the run query where those are faster (see
+ * sbf_set_insert_mode, sbf_set_query_mode); the other three keep every batch on
+ * the family's own kernels.  Every family gives bit-identical filters and
+ * answers.  Changing the family resets the tile lengths
  * (sbf_set_tile) to the new family's defaults. */
 int sbf_set_variant(sbf_filter *f, int variant);
 /* The family in effect: SBF_VARIANT_ROLLING (4-word lane kernels),

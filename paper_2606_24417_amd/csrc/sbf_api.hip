@@ -281,11 +281,15 @@ void sbf::release_stream(sbf_filter *f, hipStream_t st) {
 
 namespace {
 
+// A filter told to use the wide-shard or run-time parameter kernels does so for
+// every batch.
+bool own_kernels(const sbf_filter *f) { return f->variant == SBF_VARIANT_WIDE || f->variant == SBF_VARIANT_PARAM; }
+
 // True when an insert of len bases takes the binned kernels: the two-pass
 // strategy, unless the family's kernels are pinned.
 bool binned(const sbf_filter *f, uint64_t len, sbf::BinPlan &plan) {
   const Family fam = family(f);
-  return f->insert_mode == SBF_INSERT_TWO_PASS && !f->insert_pinned && fam != kGenericFamily &&
+  return f->insert_mode == SBF_INSERT_TWO_PASS && !f->insert_pinned && !own_kernels(f) && fam != kGenericFamily &&
          sbf::binned_plan(f->g, len, fam == kLaneFamily, plan);
 }
 
@@ -411,7 +415,7 @@ int query_kernel_mode(const sbf_filter *f) {
 // with 8- or 16-word shards a tile of more runs than its list holds (w below
 // 8) tests them in memory.
 bool by_runs(const sbf_filter *f, uint64_t n_out) {
-  if (f->query_mode != SBF_QUERY_LANE || f->query_pinned || !sbf::runs_supported(f->g)) return false;
+  if (f->query_mode != SBF_QUERY_LANE || f->query_pinned || own_kernels(f) || !sbf::runs_supported(f->g)) return false;
   const Family fam = family(f);
   if (fam == kLaneFamily) {
     const uint64_t resident = 4ull * (uint64_t)f->num_cus;
