@@ -9,7 +9,10 @@
 //   query: each lane loads its shard and tests every bit.
 // Also the small utility kernels of the library.
 #include "sbf_device.h"
+
 #include "sbf_internal.h"
+
+#include <type_traits>
 
 namespace sbf {
 namespace {
@@ -198,44 +201,67 @@ __global__ void fill_u64_kernel(uint64_t *p, uint64_t n, uint64_t v) {
 }
 
 // Record-start bits of a batch: bit off[r] for r = 1 .. nrec-1.  A workgroup
-// writes kMarkWords whole words, so nothing has to be cleared before: each of
-// its waves finds the first record at or past the words' first base (a 64-way
-// search of the sorted offsets), the lanes set the bits of the records from
-// there on in LDS, and the words are written once.  A separate clearing launch
-// and global atomic ORs took 5 + 25 us for 2M reads of 150 bp, and one launch
-// more for the smallest batches.
-constexpr int kMarkWords = 1024;
+// writes WORDS whole words, so nothing has to be cleared before: a wave
+// finds the first record at or past the words' first base (a 64-way search of
+// the sorted offsets), the lanes set the bits of the records from there on in
+// LDS, and the words are written once.  A separate clearing launch and global
+// atomic ORs took 5 + 25 us for 2M reads of 150 bp, and one launch more for the
+// smallest batches; 72 + 153 us for 10.1M records of 3 Gbp.
+// The search's probes are a cache line each, some 8 KB per workgroup, as much
+// as 2048 words: larger workgroups search less, smaller ones fill the chip.  2M
+// reads of 150 bp: 21.7, 17.4, 17.5 us with 1024, 2048, 4096 words; 0.9 Gbp of
+// 15 kbp 36, 23.7, 22.4; 3 Gbp 242, 166, 137 (8192: 151).
+// 30 Mbp take 7.2 us with 1024 and with 2048; the smallest batches, of one
+// workgroup, wait for its clearing and its writing.
+constexpr uint64_t kMarkFewWords = 1ull << 18, kMarkManyWords = 1ull << 24;
 
+template <int WORDS>
 __global__ __launch_bounds__(256) void mark_starts_kernel(const uint64_t *__restrict__ off, uint64_t nrec,
                                                           uint64_t nwords, uint64_t len,
                                                           uint32_t *__restrict__ starts) {
-  __shared__ uint32_t s_bits[kMarkWords];
+  __shared__ uint32_t s_bits[WORDS];
   const int t = threadIdx.x;
-  const uint64_t w0 = (uint64_t)blockIdx.x * kMarkWords;
-  for (int i = t; i < kMarkWords; i += 256) s_bits[i] = 0;
+  const uint64_t w0 = (uint64_t)blockIdx.x * WORDS;
   const uint64_t b0 = w0 * 32;
-  const uint64_t b1 = b0 + 32ull * kMarkWords < len ? b0 + 32ull * kMarkWords : len;
+  const uint64_t b1 = b0 + 32ull * WORDS < len ? b0 + 32ull * WORDS : len;
   // records 1 .. lo-1 start before b0, records hi .. do not
   uint64_t lo = 1, hi = nrec > 1 ? nrec : 1;
-  while (lo < hi) {
-    const uint64_t step = (hi - lo + 63) / 64;
-    const uint64_t r = lo + (uint64_t)(t & 63) * step;
-    const uint64_t before = __ballot(r < hi && off[r] < b0);
-    // the first `n` probes start before b0
-    const uint64_t n = (uint64_t)__popcll(before);
-    if (n == 0) break;
-    const uint64_t past = lo + n * step;
-    lo += (n - 1) * step + 1;
-    hi = past < hi ? past : hi;
+  auto search = [&]() {
+    while (lo < hi) {
+      const uint64_t step = (hi - lo + 63) / 64;
+      const uint64_t r = lo + (uint64_t)(t & 63) * step;
+      const uint64_t before = __ballot(r < hi && off[r] < b0);
+      // the first `n` probes start before b0
+      const uint64_t n = (uint64_t)__popcll(before);
+      if (n == 0) break;
+      const uint64_t past = lo + n * step;
+      lo += (n - 1) * step + 1;
+      hi = past < hi ? past : hi;
+    }
+  };
+  if constexpr (WORDS > 1024) {
+    // one wave searches, the others clear
+    __shared__ uint64_t s_lo;
+    if (t < 64) {
+      search();
+      if (t == 0) s_lo = lo;
+    } else {
+      for (int i = t - 64; i < WORDS; i += 192) s_bits[i] = 0;
+    }
+    __syncthreads();
+    lo = s_lo;
+  } else {
+    for (int i = t; i < WORDS; i += 256) s_bits[i] = 0;
+    search();
+    __syncthreads();
   }
-  __syncthreads();
   for (uint64_t r = lo + t; r < nrec; r += 256) {
     const uint64_t p = off[r];
     if (p >= b1) break;
     if (p >= b0) atomicOr(&s_bits[(p - b0) >> 5], 1u << (uint32_t)(p & 31u));
   }
   __syncthreads();
-  for (int i = t; i < kMarkWords; i += 256)
+  for (int i = t; i < WORDS; i += 256)
     if (w0 + i < nwords) starts[w0 + i] = s_bits[i];
 }
 
@@ -392,8 +418,17 @@ hipError_t launch_mark_record_starts(const uint64_t *off, uint64_t nrec, uint64_
                                      hipStream_t st) {
   const uint64_t nwords = (len + 31) / 32;
   if (nwords == 0) return hipSuccess;
-  hipLaunchKernelGGL(mark_starts_kernel, dim3((unsigned)((nwords + kMarkWords - 1) / kMarkWords)), dim3(256), 0, st, off,
-                     nrec, nwords, len, starts);
+  auto launch = [&](auto words) {
+    constexpr int WORDS = decltype(words)::value;
+    hipLaunchKernelGGL(mark_starts_kernel<WORDS>, dim3((unsigned)((nwords + WORDS - 1) / WORDS)), dim3(256), 0, st, off,
+                       nrec, nwords, len, starts);
+  };
+  if (nwords < kMarkFewWords)
+    launch(std::integral_constant<int, 1024>{});
+  else if (nwords < kMarkManyWords)
+    launch(std::integral_constant<int, 2048>{});
+  else
+    launch(std::integral_constant<int, 4096>{});
   return hipGetLastError();
 }
 

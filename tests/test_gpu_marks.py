@@ -55,3 +55,24 @@ def test_marks(name):
     got = buf.cpu().numpy().view(np.uint32)
     assert np.array_equal(got[:nwords], expected(off))
     assert (got[nwords:] == 0xFFFFFFFF).all(), "words past the batch written"
+
+
+# from 2^24 words (537 Mbp) on a workgroup writes 4096 words; records at the
+# edges of both sizes of block, dense at the start and sparse after
+@pytest.mark.parametrize("nwords", [(1 << 24) - 1, (1 << 24) + 5000])
+def test_marks_of_large_batches(nwords):
+    from paper_2606_24417_amd import Filter
+
+    n = nwords * 32 - 7
+    rng = np.random.default_rng(nwords)
+    edge = np.arange(32 * 2048, n - 2, 32 * 2048, dtype=np.int64)
+    cut = np.concatenate([rng.integers(1, 3_000_000, 400_000), rng.integers(1, n, 300_000), edge[::3] - 1, edge[::5],
+                          edge[::7] + 1])
+    off = np.concatenate(([0], np.sort(cut), [n])).astype(np.uint64)
+    d = torch.from_numpy(off.view(np.int64)).cuda()
+    buf = torch.full((nwords + 8,), -1, dtype=torch.int32, device="cuda")
+    Filter.mark_record_starts(d, n, starts=buf)
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy().view(np.uint32)
+    assert np.array_equal(got[:nwords], expected(off))
+    assert (got[nwords:] == 0xFFFFFFFF).all(), "words past the batch written"
