@@ -66,7 +66,9 @@ typedef struct sbf_filter sbf_filter; /* opaque; owns its device bit array */
  *   m: minimizer length, 1 <= m <= k (k-m+1 m-mers per k-mer).
  *   H: bits per s-mer, 1 <= H <= 16; hash index t uses word t mod 4.
  *   bits: requested size, 1 <= bits <= 2^40; rounded up to 256 * 2^P.
- * Allocates and zeroes the device array on the current HIP device.
+ * Allocates and zeroes the device array on the current HIP device, and with it
+ * for filters of 2 to 8 MiB the scratch that an insert of 16 bits per k-mer
+ * takes (see SBF_INSERT_TWO_PASS).
  * Returns NULL on error (SBF_E_INVAL for bad parameters, SBF_E_NOMEM when the
  * device allocation fails, SBF_E_DEVICE otherwise); nothing is left allocated
  * on failure. */

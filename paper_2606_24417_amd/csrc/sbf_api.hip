@@ -824,10 +824,17 @@ sbf_filter *sbf_create_ex(uint32_t k, uint32_t s, uint32_t m, uint32_t H, uint64
     return nullptr;
   }
   const uint64_t nwords = f->g.nshards * f->g.shard_words;
-  // filters of 2 to 8 MiB: room for the records of about 16 bits per k-mer
+  // Filters of 2 to 8 MiB: room for the records of 16 bits per k-mer, 1.2 to
+  // 2.9 times the filter, where such a batch is binned.  A scratch of its own
+  // takes 20 us more for the first insert, at 2 MiB (41 us of it and 43 of this
+  // call) and at 8 MiB (52 and 45); this call takes as long with the room and
+  // without.  Larger filters' inserts take longer than that.
   const uint64_t filter_bytes = nwords * sizeof(uint64_t);
-  const uint64_t tail_bins =
-      filter_bytes >= (2ull << 20) && filter_bytes <= (8ull << 20) ? filter_bytes + filter_bytes / 4 : 0;
+  uint64_t tail_bins = 0;
+  sbf::BinPlan first;
+  if (filter_bytes >= (2ull << 20) && filter_bytes <= (8ull << 20) &&
+      sbf::binned_plan(f->g, filter_bytes / 2 + k - 1, family(f) == kLaneFamily, first))
+    tail_bins = first.bytes;
   const uint64_t tail_at = (filter_bytes + 255) & ~255ull;
   e = hipMalloc((void **)&f->words, tail_at + 256 + tail_bins);
   if (e == hipSuccess) {

@@ -378,3 +378,37 @@ def test_scratch_is_given_back(bits):
     f.insert(d)
     assert np.array_equal(f.get_bits(), want)
     f.close()
+
+
+@pytest.mark.parametrize("k,s,m", [(31, 28, 16), (21, 15, 11), (21, 15, 16), (32, 26, 17)])
+def test_small_filters_hold_their_first_records(k, s, m):
+    """A filter of 8 MiB has room for the records of 16 bits per k-mer from its
+    creation on, whatever the window, and none where nothing is binned."""
+    from paper_2606_24417_amd import Filter
+
+    n = (1 << 22) + k - 1
+    seq = synth.background(n, 98)
+    d = dev(seq)
+
+    def used(H, insert):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        fs = [Filter(k, s, m, H, 1 << 26) for _ in range(8)]
+        created = before - torch.cuda.mem_get_info()[0]
+        if insert:
+            for f in fs:
+                f.insert(d)
+            torch.cuda.synchronize()
+        inserted = before - torch.cuda.mem_get_info()[0]
+        words = fs[0].get_bits()
+        for f in fs:
+            f.close()
+        return created, inserted, words
+
+    used(4, True)  # the library's own allocations of a first run
+    created, inserted, words = used(4, True)
+    print("8 filters: %.1f MiB created, %.1f after inserts" % (created / 2**20, inserted / 2**20), flush=True)
+    assert inserted == created
+    p = oracle.Params(k, s, m, 4, 1 << 26)
+    assert np.array_equal(words, oracle.insert(p, p.empty(), seq))
+    assert used(9, False)[0] <= 8 * (12 << 20)  # generic kernels: 8 MiB and a granule each
