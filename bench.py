@@ -36,6 +36,10 @@ PEAK_INT_TOPS = 39.3216      # 256 CU x 4 SIMD x 16 lanes x 2.4 GHz, 32-bit inte
 # s-mer hash 10, H=4 bit addresses 4; insert adds one-hot + segment OR 16,
 # query adds the (k-s+1)*H = 16 bit tests at 2 ops each plus the output 1)
 OPS_PER_KMER = {"insert": 46, "query": 63}
+# Launches of a binned insert: the counters' clearing and the bin pass, then a
+# split and an apply launch per group of buckets (one group, and 16 for 3 Gbp
+# into 8 GiB; tests/test_binned_plan.py holds them against the library's plan).
+BINNED_LAUNCHES = {"in_cache": 4, "out_of_cache": 34}
 KERNEL_SOURCES = ["paper_2606_24417_amd/csrc/kernels_rolling.hip", "paper_2606_24417_amd/csrc/kernels_wide.hip",
                   "paper_2606_24417_amd/csrc/sbf_tiles.h", "paper_2606_24417_amd/csrc/sbf_device.h",
                   "paper_2606_24417_amd/csrc/sbf_segments.h", "paper_2606_24417_amd/csrc/sbf_runs.h",
@@ -1126,9 +1130,7 @@ def measure(args, name, with_cpu):
     roof_q["kernel"] = q_kernel
     ins_kernel = ins_kernels[0] if ins_launches == 2 else ins_kernels[1]
     if binned:
-        # the counters' clearing and the bin pass, then a split and an apply
-        # launch per group of buckets: one in cache, 16 for the 8 GiB filter
-        ins_launches = 4 if in_cache else 34
+        ins_launches = BINNED_LAUNCHES["in_cache" if in_cache else "out_of_cache"]
     roof_i = roofline("insert", i_mean, n_ins_kmers, ins_launches)
     roof_i["kernel"] = ins_kernel
     if q_mean >= i_mean / ins_launches:

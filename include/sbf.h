@@ -160,7 +160,9 @@ int sbf_query_batch(sbf_filter *f, const char *seq, const uint64_t *off, uint64_
 /* Device form: d_seq holds len = off[nrec] bases, d_off is a device array of
  * nrec+1 offsets (not read by the host, so it is not validated: off[0] must
  * be 0 and off[nrec] must equal len).  Stream-ordered.  The library keeps one
- * scratch buffer of len/8 bytes per stream used (record starts as bits).
+ * scratch buffer of len/8 bytes per stream used (record starts as bits); a batch
+ * longer than those before on its stream waits for that stream and allocates
+ * a larger one.
  * Queries on different streams may overlap one another; inserts into one
  * filter must not overlap another insert under SBF_INSERT_TWO_PASS (a store
  * of one could undo a bit the other has already repaired): order them
@@ -179,8 +181,8 @@ int sbf_query_batch_dev(sbf_filter *f, const char *d_seq, uint64_t len, const ui
  * bases (len > 2^26 returns SBF_E_INVAL).  The array is shared by every call
  * on that GPU, whatever the filter or stream: calls that overlap on one GPU
  * (on different streams, or from several host threads) race and must be
- * ordered by the caller.  The scratch is cleared by fill kernels on `stream`
- * (no memset), and the filter's launch settings apply.  Stream-ordered. */
+ * ordered by the caller.  The scratch is written by kernels on `stream` (no
+ * memset), and the filter's launch settings apply.  Stream-ordered. */
 int sbf_query_batch_dev_noalloc(sbf_filter *f, const char *d_seq, uint64_t len, const uint64_t *d_off,
                                 uint64_t nrec, uint8_t *d_out, void *stream);
 

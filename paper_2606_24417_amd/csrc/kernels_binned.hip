@@ -39,14 +39,7 @@ constexpr int kMaxBucketBits2 = 11;
 constexpr int kSplitWG = 512;
 constexpr int kSplitPer = 8;                // records per lane
 constexpr int kSplitTile = kSplitWG * kSplitPer;
-#ifndef SWB
-#define SWB 13
-#define AWG 512
-#define COH 1
-#endif
-constexpr int kSliceWordBits = SWB;          // a slice is 2^13 words: 64 KB
-constexpr int kSliceWords = 1 << kSliceWordBits;
-constexpr uint32_t kApplyGrid = 512 << (13-SWB);        // two workgroups per CU (64 KB of LDS each)
+constexpr uint32_t kApplyGrid = 512;        // two workgroups per CU (64 KB of LDS each), four of 32 KB
 
 // k-mers binned at a time: up to these, more for a filter that has more memory
 // itself
@@ -180,6 +173,8 @@ __device__ __forceinline__ void apply_overflow(const Record (&rec)[N], uint32_t 
 // k-mers appends less than four at a time to each, lines leave the L2 before
 // they are full and the pass writes 1.5 times its records (3 Gbp: 4.65 ms
 // with 256 lanes, 3.41 with 512; with 128 buckets 100 Mbp 0.113 and 0.120).
+// LDS allows four workgroups of 256 lanes per CU, or two of 512; three of 256
+// for w below 11, whose list is longer.
 template <int W, int MK, int WG>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void bin_kernel(
     const uint8_t *__restrict__ seq, uint64_t len, const uint32_t *__restrict__ starts, int aligned16, RunGeo P,

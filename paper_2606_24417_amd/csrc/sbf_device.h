@@ -206,13 +206,18 @@ __device__ __forceinline__ uint64_t pair_swap64(uint64_t x) {
   return ((uint64_t)pair_swap((uint32_t)(x >> 32)) << 32) | pair_swap((uint32_t)x);
 }
 
-// Every workgroup of the insert, repair and query kernels starts with an
-// agent-scope acquire (buffer_inv sc1: its XCD's L2 drops its lines), so
-// that no load of the launch returns a copy cached before it.  Within a
-// launch a plain load may then only miss bits that other workgroups are
-// adding at the same time: the store pass loses them to a racing update and
-// the repair walk restores them, and the repair walk, whose plain loads race
-// only with its own atomic ORs, at worst repeats an OR.
+// Every workgroup of the insert, repair, apply and query kernels starts with an
+// agent-scope acquire (buffer_inv sc1: its XCD's L2 drops its lines) before its
+// first access to the filter.  What earlier launches on the stream wrote is
+// visible without it: a dispatch releases its writes to the device at its end
+// and acquires at its start.  The loads of sequence, start bits, records and
+// counters, which may run before the acquire or (bin and split kernels) without
+// one, rest on that alone; so could the filter's.  The acquire stays on them
+// because the exactness of the store and repair passes across XCDs was
+// established with it.  Within a launch a plain load may miss bits that other
+// workgroups are adding at the same time: the store pass loses them to a racing
+// update and the repair walk restores them, and the repair walk, whose plain
+// loads race only with its own atomic ORs, at worst repeats an OR.
 // One wave of the workgroup executes it (the caches are the CU's and the
 // XCD's, not the wave's) and waits for it; the workgroup's next barrier, which
 // every kernel has before its first filter access, holds the others.  Each

@@ -24,7 +24,7 @@ struct SeqArgs {
   uint8_t *out;            // query only
   uint64_t n_out;          // query only
   // query only: out holds one bit per k-mer start (bit i%8 of byte i/8), ceil(n_out/8) bytes;
-  // supported by the lane-sequential rolling query only (query_packed_supported)
+  // supported by the lane-sequential rolling query (query_packed_supported) and the run query
   int packed = 0;
 };
 

@@ -1,7 +1,7 @@
-// Front end of the run kernels (kernels_binned.hip, kernels_runs.hip): a
-// workgroup stages a tile of WG x 32 k-mers, computes every k-mer's shard and
-// finds the runs of consecutive valid k-mers with one shard (super-k-mers),
-// cut to at most nmax k-mers.  Lane t owns k-mers 32t .. 32t+31; the sliding
+// Front end of the run kernels (kernels_binned.hip, query_runs.h): a workgroup
+// stages a tile of WG x 32 k-mers, computes every k-mer's shard and finds the
+// runs of consecutive valid k-mers with one shard (super-k-mers), cut to at most
+// nmax k-mers.  Lane t owns k-mers 32t .. 32t+31; the sliding
 // minimum over its m-mer hashes is a van Herk / Gil-Werman minimum held in
 // registers (w = k-m+1 is a compile-time constant, k and m are not).
 #pragma once
@@ -341,7 +341,10 @@ inline int run_mk(uint32_t k, uint32_t m) { return m > 16 ? 2 : k == 31 && m == 
 
 // Compiled (w, m class) pairs: m = 16 at k = 31, and every w = k - m + 1 from
 // 6 on for m <= 16 (MK 1) and m > 16 (MK 2).  Below 6 a batch has a record
-// for every third k-mer or more.
+// for every third k-mer or more.  Each w is its own unrolled minimum in
+// registers; the 39 pairs times two tiles of the bin kernel and two query
+// kernels per shard size make up most of the library (2.4 MB without them,
+// 11.3 with) and of its build.
 #define SBF_RUN_SETS(X)                                                                                  \
   X(16, 0) X(6, 1) X(7, 1) X(8, 1) X(9, 1) X(10, 1) X(11, 1) X(12, 1) X(13, 1) X(14, 1) X(15, 1)          \
   X(16, 1) X(17, 1) X(18, 1) X(19, 1) X(20, 1) X(21, 1) X(22, 1) X(23, 1) X(24, 1) X(25, 1) X(26, 1)      \

@@ -76,3 +76,15 @@ def test_scratch_stays_within_its_bound(log2_bits, S):
             parts = -(-nk // p.chunk)
             assert 0 <= p.chunk * parts - nk < 16384 * (parts + 1)
     assert planned >= 20
+
+
+# The launches that the benchmark states for its two workloads: 100 Mbp into 2^31
+# bits and 3 Gbp into 2^36, in one part.
+@pytest.mark.parametrize("name,bits,length", [("in_cache", 1 << 31, 100_000_000), ("out_of_cache", 1 << 36, 3_000_000_000)])
+@pytest.mark.parametrize("S", [4, 8, 16])
+def test_launches_of_the_benchmark(S, name, bits, length):
+    import bench
+
+    p = plan(31, 28, 16, 4, bits, S, length, lane_family=S == 4)
+    assert p.chunk >= length - 30 and p.bits2 > 0
+    assert 2 + 2 * ((1 << p.bits1) // p.group) == bench.BINNED_LAUNCHES[name]
