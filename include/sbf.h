@@ -318,7 +318,7 @@ void sbf_graph_destroy(sbf_graph *g);
  * and restored afterwards (f's contents are unchanged; the buffer must fit in
  * device memory), then apply the fastest settings to f.  The family's own
  * kernels take every later batch only where they beat the binned insert or the
- * run query here; tuned on batches that take neither, f still picks by size, as
+ * run query here by 5% or more; tuned on batches that take neither, f still picks by size, as
  * at the default tile.  (Where SBF_INSERT_ATOMIC is fastest, as for batches of
  * some 100000 k-mers, it holds for every later insert: tune on a batch like
  * those to come.)  A text report of

@@ -1449,7 +1449,10 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
   };
   float best_ins = 1e30f, best_q = 1e30f;
   // the family's kernels stay pinned only if they beat the binned insert or
-  // the run query on these batches: others, of other sizes, keep the choice
+  // the run query on these batches: others, of other sizes, keep the choice.
+  // Leaving those, or the lane organisation, takes 5%, more than the trials of
+  // small batches differ by themselves.
+  constexpr float kClear = 0.95f;
   bool tried_binned = false, best_binned = false, tried_runs = false, best_runs = false;
   int bi_mode = f->insert_mode, bq_mode = f->query_mode;
   uint32_t bi_shape = f->insert_wgs_per_cu, bq_shape = f->query_wgs_per_cu, bi_len = 0, bq_len = 0;
@@ -1502,7 +1505,7 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
           line("insert %-8s %2u k-mers/lane, workgroups/CU %u%s: %.4f ms\n",
                mode == SBF_INSERT_ATOMIC ? "atomic" : "two-pass", lane_len_effective(t, len, true), sh,
                sh ? "" : " (one per tile)", ms);
-          if (ms < best_ins) {
+          if (ms < (best_binned ? kClear : 1.f) * best_ins) {
             best_ins = ms;
             bi_mode = mode;
             bi_shape = sh;
@@ -1550,7 +1553,8 @@ int autotune_filter(sbf_filter *f, const Batch &ins, const Batch &q, std::string
                wide ? wide_name : mode == SBF_QUERY_LANE ? "lane" : mode == SBF_QUERY_LEADER ? "leader" : "direct",
                mode == SBF_QUERY_LANE ? lane_len_effective(t, len, false) : 16u, sh, sh ? "" : " (one per tile)",
                ms);
-          if (ms < best_q) {
+          const bool leaves = best_runs || (mode != SBF_QUERY_LANE && bq_mode == SBF_QUERY_LANE);
+          if (ms < (leaves ? kClear : 1.f) * best_q) {
             best_q = ms;
             bq_mode = mode;
             bq_shape = sh;
