@@ -20,7 +20,7 @@
 // and applied with atomic ORs of the bits that are missing, before any slice is
 // read.
 // Measured against the two passes (clear + insert): 100 Mbp into 256 MiB 880
-// -> 412 us, with 16-word shards 2159 -> 475, 3 Gbp into 8 GiB 29.8 -> 13.7 ms,
+// -> 412 us, with 16-word shards 2159 -> 468, 3 Gbp into 8 GiB 29.8 -> 13.6 ms,
 // 1 Mbp into 2 MiB 76 -> 25 us.
 #include "sbf_runs.h"
 
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(kSplitWG) __attribute__((amdgpu_waves_per_eu(4))) v
 // (slice - s0) * regions on; counts are indexed from slice 0.  The records are
 // taken in order of length (a counting sort of their indices), so that the
 // lanes of a wave finish together (320 -> 254 us for 100 Mbp, with fewer, larger
-// launches; 199 us now, 42 VALU instructions per k-mer at 55% of issue: a
+// launches; 198 us now, 42 VALU instructions per k-mer at 56% of issue: a
 // workgroup waits between its sort, its records and its write-back, and four
 // per CU do not hide all of it).
 // With 8- and 16-word shards, whose bits are ORed one by one, sector c of shard
@@ -510,7 +510,8 @@ __global__ __launch_bounds__(1 << (SB - 4)) __attribute__((amdgpu_waves_per_eu(4
     const int count = (int)(r[2] & 15u) + 1 + B.z;
     uint32_t x = r[0], y = r[1], w = r[2];
     uint64_t m[4] = {0, 0, 0, 0};
-// (unrolled by 2, the bit by bit ORs of 100 Mbp take 470 us instead of 457)
+    // (unrolled by 2, clear + insert of 100 Mbp into 16-word shards take 470 us
+    // instead of 457)
 #pragma unroll (SW > 4 ? 4 : 2)
     for (int j = 0; j < count; ++j) {
       const uint64_t g = top_smer_hash<S>(x, y, B);

@@ -10,10 +10,11 @@
 // Answers are collected as bits in LDS and written as bytes (or bits), 32
 // k-mers per lane.
 // Bound by VALU issue in cache (62 instructions per position at 80%, the lane
-// kernel 73 at 70%) and by a 128-byte line per super-k-mer out of cache (5.2
-// TB/s).  2M reads of 150 bp: 865 -> 666 us (4-word shards), 2004 -> 882 (16
-// words); 150 Mbp at k = 21 1282 -> 502 us (before: the run-time parameter
-// kernel); 3 Gbp of reads against 8 GiB 9.99 -> 9.19 ms.
+// kernel 73 at 70%) and by random reads out of cache: 35 G super-k-mers/s, where
+// two 16-byte loads per lane reach 41 G shards/s and lane pairs 48.7, each of
+// them a 128-byte line (5.2 TB/s).  2M reads of 150 bp: 865 -> 654 us (4-word shards), 2004 -> 873 (16
+// words); 150 Mbp at k = 21 1282 -> 497 us (before: the run-time parameter
+// kernel); 3 Gbp of reads against 8 GiB 9.99 -> 9.07 ms.
 #pragma once
 
 #include "sbf_runs.h"

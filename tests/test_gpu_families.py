@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-from paper_2606_24417_amd.sbf import (VARIANT_AUTO, VARIANT_PARAM, VARIANT_ROLLING, VARIANT_WIDE,  # noqa: E402
+from paper_2606_24417_amd.sbf import (VARIANT_AUTO, VARIANT_GENERIC, VARIANT_PARAM, VARIANT_ROLLING, VARIANT_WIDE,  # noqa: E402
                                       Filter)
 
 
@@ -148,3 +148,26 @@ def test_lane_validity_at_window_seams(lane):
     off = np.array([0] + starts + [n], dtype=np.uint64)
     want = against_oracle((31, 28, 16, 4, 1 << 23), 4, (seq, off), (seq, off), tile=(32, lane))
     assert want.sum() > n // 2
+
+
+# The generic query on a batch that fills the GPU many times over, three times,
+# against the default kernels (which the full-size tests compare with the
+# oracle), and the filter that the generic insert builds.
+@pytest.mark.parametrize("S", [4, 8, 16])
+@pytest.mark.parametrize("k,s,m,H", [(31, 28, 16, 4), (21, 15, 11, 8)])
+def test_generic_kernels_on_large_batches(k, s, m, H, S):
+    print("case generic large", k, s, m, H, S, flush=True)
+    w = synth.in_cache_workload(scale=0.1)
+    d, o = dev(w["insert"][0]), doff(w["insert"][1])
+    q, qo = dev(w["query"][0]), doff(w["query"][1])
+    f, g = Filter(k, s, m, H, w["bits"], shard_words=S), Filter(k, s, m, H, w["bits"], shard_words=S)
+    g.variant = VARIANT_GENERIC
+    f.insert(d, o)
+    g.insert(d, o)
+    assert np.array_equal(f.get_bits(), g.get_bits())
+    for off in (qo, None):
+        want = f.query(q, off)
+        for _ in range(3):
+            assert torch.equal(g.query(q, off), want)
+    f.close()
+    g.close()
