@@ -733,7 +733,7 @@ def bench_sweep(args):
     # shard geometry (4, 8, 16 words per shard) at (28, 16, 4), each with the
     # library's choice (binned insert, run query) and with every family that
     # runs it (the lane kernels by their tile)
-    geometry = []
+    geometry, same_geometry = [], True
     for S, variants in ((4, (0, 1, 4, 2)), (8, (0, 3, 4, 2)), (16, (0, 3, 4, 2))):
         for variant in variants:
             f = Filter(k, 28, 16, 4, w["bits"], shard_words=S)
@@ -741,6 +741,9 @@ def bench_sweep(args):
             if variant == VARIANT_ROLLING:
                 f.set_tile(64, 48)
             ti, tq = timed(f, d_out)
+            if variant == 0:
+                d_ref.copy_(d_out)
+            same_geometry = same_geometry and bool(torch.equal(d_out, d_ref))
             geometry.append({"shard_words": S, "kernels": FAMILY_NAMES[variant] if variant else "default",
                              "filter_bits": f.num_bits,
                              "fpr": int(d_out[neg0:].sum().item()) / max(1, neg_kmers), "insert_ms": ti,
@@ -752,7 +755,8 @@ def bench_sweep(args):
     fastest = min(rows, key=lambda r: r["param_insert_ms"] + r["param_query_ms"])
     res = {"metric": "sweep: FPR and insert/query kernel ms per (s,m,H) at k=31, 16 bits per k-mer",
            "unit": "fpr", "points": len(rows), "zero_false_negatives_everywhere": all_ok,
-           "default_and_param_answers_equal": same, "best_fpr": best, "fastest_param": fastest,
+           "default_and_param_answers_equal": same, "geometry_answers_equal": same_geometry,
+           "best_fpr": best, "fastest_param": fastest,
            "at_28_16_4": next((r for r in rows if (r["s"], r["m"], r["H"]) == (28, 16, 4)), None),
            "rows": rows, "geometry": geometry,
            "config": {"workload": w["name"] + " (scale %g)" % args.scale, "filter_bits": w["bits"],
